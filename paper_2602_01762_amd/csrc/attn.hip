@@ -595,7 +595,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
   float sum = 0.f;
   for (int gg = 0; gg < G; ++gg) sum += red[gg * d + dim];
   const float v = lsum > 0.f ? sum / lsum : 0.f;
-  const size_t i = (size_t)r * a.o.ld + (size_t)h * d + dim;
+  const size_t i = a.o.at(r, h * d + dim);
   if constexpr (sizeof(T) == 2) {
     const uint32_t hb = f2bf(v);
     ((bf16_t *)a.o.hi)[i] = (bf16_t)hb;
@@ -652,7 +652,7 @@ __global__ __launch_bounds__(256) void k_attn_combine_w(AttnArgs a) {
     const int dim = lane + 64 * j;
     if (dim >= d) break;
     const float v = lsum > 0.f ? o[j] / lsum : 0.f;
-    const size_t i = (size_t)r * a.o.ld + (size_t)h * d + dim;
+    const size_t i = a.o.at(r, h * d + dim);
     if constexpr (sizeof(T) == 2) {
       const uint32_t hb = f2bf(v);
       ((bf16_t *)a.o.hi)[i] = (bf16_t)hb;

@@ -45,15 +45,29 @@ struct TiledMat {
 // and `lo` is null.  bf16 models: the fp32 value x is carried as the pair
 // hi = bf16(x), lo = bf16(x - hi) (two planes), both fed to the MFMA, so the
 // product sees x to within 2^-17 relative.
+//
+// Passes of more than MAX_ROWS rows (bf16) keep the planes tiled (pk): the
+// 16 rows x 32 columns of one MFMA B fragment are one contiguous KiB in
+// operand order, [rows / 16][ld / 32][64 lanes][8 values], so that the tile
+// kernel moves a fragment to LDS with one coalesced load per wave.  The rows
+// of the last tile past R are allocated and hold anything: column j of a
+// product reaches output row j only, which is not stored.
 struct Act {
   const void *hi = nullptr;
   const void *lo = nullptr;
   int ld = 0;
+  int pk = 0;
 };
 struct ActOut {
   void *hi = nullptr;
   void *lo = nullptr;
   int ld = 0;
+  int pk = 0;
+  // element (r, c); 8 columns from a multiple of 8 are contiguous either way
+  __host__ __device__ size_t at(int r, int c) const {
+    if (!pk) return (size_t)r * ld + c;
+    return ((size_t)(r >> 4) * (ld >> 5) + (c >> 5)) * 512 + ((c >> 3) & 3) * 128 + (r & 15) * 8 + (c & 7);
+  }
 };
 
 // Row norms: the producer of a vector x writes, per 16-feature tile t and
@@ -86,8 +100,8 @@ struct RowsIn {
   const uint64_t *bits;
 };
 
-// EPI_STORE (row-group kernel only): y = scale * acc, nothing else (the LM
-// head of a tree-scoring pass)
+// EPI_STORE (tile kernel only): y = scale * acc, nothing else (the LM head
+// of a tree-scoring pass, the embedding tables)
 enum Epi { EPI_NORM = 0, EPI_SWIGLU = 1, EPI_QKV = 2, EPI_STORE = 3 };
 
 // Token of each row taken straight from the previous LM head's top-1
@@ -118,8 +132,12 @@ struct GemmLaunch {
   int nt;          // tiles per workgroup (1 or 2)
   int gemv;        // 1: VALU GEMV main loop (bf16, R <= 4, staged fp32 activations)
   int split;       // > 0: batched path, K split over `split` workgroup slices
-  int rowgrp;      // 1: more than MAX_ROWS rows: the row-group kernel (k_gemm_rows), split slices
+  int rowgrp;      // 1: more than MAX_ROWS rows: the tile kernel, split slices
+  int tile0;       // first tile of m in the full QKV product (EPI_QKV of its q or its k, v rows)
   float *part;     // batched path: slice partial sums [split][R][N]
+  // the product ran on fewer rows than the finish pass writes: row r takes
+  // partial row r / part_div of part_rows (0: the same rows)
+  int part_div, part_rows;
   int epi;
   RowNorm norm;    // scale rows of the result (SWIGLU, QKV); n_parts = 0: none
   // EPI_NORM: y = acc (+ res) -> y [R, ldy] fp32; (y * gain) -> g planes; ss
@@ -143,7 +161,10 @@ struct GemmLaunch {
   // embedding half W_fc[:, :H] E[token] precomputed for every token
   const float *tab;
   int kb_lo;
-  const int32_t *tab_tok;   // batched path: each row's token (-1: none), written by the FC prep
+  int kb_n;                 // tile kernel: k-blocks [kb_lo, kb_lo + kb_n) only (0: to the end)
+  const int32_t *tab_tok;   // batched path: each row's token (-1: none), written by the FC prep,
+                            // or (tab_V > 0) as the caller gave it, checked against tab_V ids
+  int tab_V;
   // chain steps >= 2 without an FC prep pass: the previous step's down
   // product also writes its output y as operand planes (yx.hi != NULL), and
   // wave 0 of K-split workgroup i < R resolves row i's token (from gx.lm, or
@@ -173,17 +194,21 @@ struct LmLaunch {
 bool launch_gemm(bool bf16, const GemmLaunch &g, hipStream_t s);
 void launch_lmhead(bool bf16, const LmLaunch &g, hipStream_t s);
 // LM head over up to LMR_MAX_ROWS rows in one launch, logits only (bf16,
-// the row-group product kernel): logits[r][v] = scale[r] * (W x_r)[v]
+// the tile kernel): logits[r][v] = scale[r] * (W x_r)[v]
 constexpr int LMR_MAX_ROWS = 256;
 struct LmRowsArgs {
   TiledMat m;
-  Act x;                  // [R, H] hi/lo planes
+  Act x;                  // [R, H] tiled hi/lo planes
   int R;
   const float *scale;     // [R] row scales, or NULL
   float *logits; long ld_logits;
 };
-bool lmhead_rows_fits(const TiledMat &m, int R);
 void launch_lmhead_rows(const LmRowsArgs &g, hipStream_t s);
+// finish pass alone over g.R rows, of slice partials that an earlier product
+// left in g.part (EPI_NORM)
+void launch_gemm_finish(const GemmLaunch &g, hipStream_t s);
+// the product alone (K slices to g.part), without its finish pass
+bool launch_gemm_slices(const GemmLaunch &g, hipStream_t s);
 int lm_workgroups(int n_tiles, int nt);
 // partial sums of squares per row that an EPI_NORM launch writes
 int gemm_ss_parts(const GemmLaunch &g);
@@ -244,7 +269,7 @@ void launch_verify_tree(int B, int nodes, int V, const float *tl, const int32_t 
                         void *stats, hipStream_t s);
 // T[v][n] = sum_{k < H} W[n][k] E[v][k] for every token v: the embedding
 // half of a fusion FC in the tiled layout (k-blocks [0, H / 32) of each tile)
-// times the embedding rows, fp32 [V, N]; N a multiple of 64
+// times the embedding rows, fp32 [V, N]
 void launch_embed_table(const TiledMat &w, const void *embed, int V, int H, float *T, hipStream_t s);
 // top-k partials from stored logits [R, ld] (rows whose LM head skips its
 // epilogue): n_wg = lm_topk_chunks(V) chunks per row, topk <= TK_MAXK, in the
@@ -282,6 +307,21 @@ struct RowsGather {
   int n[2];
 };
 void launch_rows_gather(int rows, const RowsGather &a, hipStream_t s);
+// The last accepted row of each sequence, of the rows r0 .. r0 + n_src - 1 of
+// u [*, H] (the fusion FC's output) that hold it: destination row b = u row
+// idx[b] - r0 -> dst [rows, H], (u * gain) as row-major hi/lo planes x, and
+// the RMSNorm scale of the row; idx[b] = -1: zeros (on the call with r0 = 0).
+struct LastRows {
+  const int32_t *idx;
+  int r0, n_src, H;
+  float eps;
+  const float *u;
+  const void *gain;
+  float *dst;
+  ActOut x;
+  float *scale;
+};
+void launch_last_rows(int rows, const LastRows &a, hipStream_t s);
 // tree bookkeeping
 struct TreeWs {
   int B, w, D, C;                 // batch, width, depth, candidates per sequence

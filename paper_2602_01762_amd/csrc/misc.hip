@@ -43,7 +43,7 @@ __global__ __launch_bounds__(256) void k_fc_prep(FcPrepArgs a) {
   }
   if (a.tok_out && e0 == 0) a.tok_out[r] = tok;
   if (e0 >= a.H + a.F || (a.feat_only && e0 < a.H)) return;
-  const size_t o = (size_t)r * a.X.ld + e0;
+  const size_t o = a.X.at(r, e0);
   float v[8];
   bool exact;   // value already representable in the storage type
   if (e0 < a.H) {
@@ -701,6 +701,34 @@ __global__ void k_rows_gather(RowsGather a) {
 void launch_rows_gather(int rows, const RowsGather &a, hipStream_t s) {
   const int n = a.n[0] > a.n[1] ? a.n[0] : a.n[1];
   hipLaunchKernelGGL(k_rows_gather, dim3((n + 255) / 256, rows, 2), dim3(256), 0, s, a);
+}
+
+// One workgroup per sequence whose last row is among those given: the row is
+// read once, its sum of squares by the block (fixed order), and written out
+// with its operand planes.
+__global__ __launch_bounds__(256) void k_last_rows(LastRows a) {
+  __shared__ float sh[8];
+  const int b = blockIdx.x;
+  const int src = a.idx[b], rel = src - a.r0;
+  if (src < 0 ? a.r0 != 0 : (rel < 0 || rel >= a.n_src)) return;   // uniform
+  const float *u = a.u + (size_t)(src < 0 ? 0 : rel) * a.H;
+  float ss = 0.f;
+  for (int c = threadIdx.x; c < a.H; c += 256) {
+    const float v = src < 0 ? 0.f : u[c];
+    a.dst[(size_t)b * a.H + c] = v;
+    const float x = v * Ty<bf16_t>::ld((const bf16_t *)a.gain, c);
+    const size_t i = a.x.at(b, c);
+    const uint32_t h = f2bf(x);
+    ((bf16_t *)a.x.hi)[i] = (bf16_t)h;
+    ((bf16_t *)a.x.lo)[i] = (bf16_t)f2bf(x - bf2f(h));
+    ss += v * v;
+  }
+  const float tot = block_sum(ss, sh);
+  if (threadIdx.x == 0) a.scale[b] = 1.0f / sqrtf(tot / (float)a.H + a.eps);
+}
+
+void launch_last_rows(int rows, const LastRows &a, hipStream_t s) {
+  hipLaunchKernelGGL(k_last_rows, dim3(rows), dim3(256), 0, s, a);
 }
 
 // ---------------------------------------------------------------------------

@@ -42,23 +42,37 @@ struct ProductPlan {
   int nt = 1;      // output tiles per wave
   int split = 0;   // > 0: K slices across workgroups (batched path, then a finish pass)
   int gemv = 0;    // 1: VALU GEMV main loop (bf16, at most GEMV_MAX_ROWS rows)
-  int rowgrp = 0;  // 1: row-group kernel (more than MAX_ROWS rows, bf16), K slices, finish pass
+  int rowgrp = 0;  // 1: tile kernel (more than MAX_ROWS rows, bf16), K slices, finish pass
 };
 
-// Products over more than MAX_ROWS rows (tree-scoring passes of whole trees,
-// bf16, up to ROWGRP_MAX_ROWS rows): workgroups of 4 waves take
-// ROWGRP_TILES output tiles against one group of ROWGRP_ROWS rows over one K
-// slice.  Slices: about ROWGRP_WGS workgroups in all (two per CU), at least
-// 4 k-blocks each.
-constexpr int ROWGRP_MAX_ROWS = 256;
+// Products over more than MAX_ROWS rows (bf16: tree-scoring passes of whole
+// trees up to 256 rows, the front of a long catch-up): the tile kernel.  A
+// workgroup of 8 waves takes ROWGRP_TILES output tiles (256 features)
+// against 128 or 64 rows over one K slice.  Slices: up to 256 rows about
+// ROWGRP_WGS units of ROWGRP_TILES tiles x ROWGRP_ROWS rows in all (256
+// workgroups of 128 rows, one per CU), at least 4 k-blocks each; above, as
+// many as keep the 128-row grid within the 256 CUs (a grid just above them
+// runs a second, nearly empty round).
+constexpr int ROWGRP_MAX_ROWS = 2048;
 constexpr int ROWGRP_TILES = 16;
 constexpr int ROWGRP_ROWS = 64;
 constexpr int ROWGRP_WGS = 512;
 inline int rowgrp_split(int n_tiles, int nkb, int R) {
-  const int base = (n_tiles + ROWGRP_TILES - 1) / ROWGRP_TILES * ((R + ROWGRP_ROWS - 1) / ROWGRP_ROWS);
-  int sp = (ROWGRP_WGS + base / 2) / base;
+  const int xg = (n_tiles + ROWGRP_TILES - 1) / ROWGRP_TILES;
+  const int base = xg * ((R + ROWGRP_ROWS - 1) / ROWGRP_ROWS);
+  int sp = R > 256 ? 256 / (xg * ((R + 127) / 128)) : (ROWGRP_WGS + base / 2) / base;
   if (sp > nkb / 4) sp = nkb / 4;
   return sp < 1 ? 1 : sp;
+}
+
+// Rows per workgroup (128 or 64) of a row-group product: whichever takes
+// fewer rounds of the 256 CUs, a 64-row round costing 0.59 of a 128-row one
+// (8B LM head over 244 rows, 501 tile groups: 489 us in 8 rounds against
+// 413 us in 4).
+inline int rowgrp_rows(int n_tiles, int R, int split) {
+  const long xg = (long)((n_tiles + ROWGRP_TILES - 1) / ROWGRP_TILES) * split;
+  const long r128 = (xg * ((R + 127) / 128) + 255) / 256, r64 = (xg * ((R + 63) / 64) + 255) / 256;
+  return r64 * 59 < r128 * 100 ? 64 : 128;
 }
 
 // K slices of a batched product at nt tiles per wave: at most one workgroup
@@ -111,7 +125,7 @@ inline ProductPlan plan_product(int n_tiles, int nkb, int K, int K_full, int R, 
                                 bool bf16, size_t lds_limit) {
   ProductPlan p;
   const int rt = row_tiles(R);
-  if (R > MAX_ROWS) {   // the row-group kernel (bf16 only: fp32 passes stay within MAX_ROWS)
+  if (R > MAX_ROWS) {   // the tile kernel (bf16 only: fp32 passes stay within MAX_ROWS)
     p.rowgrp = bf16 ? 1 : 0;
     p.nt = 4;
     p.split = rowgrp_split(n_tiles, nkb, R);
@@ -160,13 +174,14 @@ inline ProductPlan plan_product(int n_tiles, int nkb, int K, int K_full, int R, 
 
 // fp32 words of the K-slice partial sums ([split][rows][N]) that any
 // batched product of an [N = 16 n_tiles, K] matrix (nkb k-blocks) writes at
-// GEMV_MAX_ROWS + 1 .. rows_max rows.  The slices depend on the row count
+// 1 .. rows_max rows (a tree-scoring pass slices the fusion FC over its
+// sequences' feature rows, however few).  The slices depend on the row count
 // and the tiles per wave and do not shrink as K grows, so the full K bounds
 // the fusion FC's feature-column products too.
 inline size_t product_partial_floats(int n_tiles, int nkb, int K, int rows_max) {
   size_t most = 0;
   const size_t N = (size_t)16 * n_tiles;
-  for (int rr = GEMV_MAX_ROWS + 1; rr <= rows_max; ++rr) {
+  for (int rr = 1; rr <= rows_max; ++rr) {
     int sp = 0;
     if (rr > MAX_ROWS) {
       sp = rowgrp_split(n_tiles, nkb, rr);

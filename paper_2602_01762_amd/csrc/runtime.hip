@@ -50,6 +50,9 @@ struct Pass {            // one forward pass: where its inputs and outputs live
   // pass's down product and its tokens in its own K-split kernel (no prep
   // pass); this pass's down product writes that operand for the next pass
   bool op_in, op_out;
+  // tree scoring: > 0: every fc_div rows share one feature row (a tree's), and
+  // the fusion FC multiplies those R / fc_div rows only
+  int fc_div;
   // tree scoring (lm_rows_x.hi != NULL): no LM head in the pass; its
   // operand rows and row scales go here, for the caller's LM head over them
   ActOut lm_rows_x;
@@ -70,8 +73,8 @@ struct prism_ctx {
   int H = 0, nq = 0, nkv = 0, d = 0, I = 0, V = 0, QKV = 0;
   int rows_max = 0, max_slots = 0, kmax = 1, n_wg_lm = 0, Cmax = 0;
   // rows of the largest pass: tree scoring (bf16) runs whole trees in passes
-  // of up to LMR_MAX_ROWS rows (the row-group products and one LM head per
-  // pass); other passes take at most rows_max
+  // of up to LMR_MAX_ROWS rows (the tile kernel's products and one LM head
+  // per pass); other passes take at most rows_max
   int pass_max = 0;
   int score_grp = 1;                // tree scoring: rows per attention workgroup
   int feat_max = 0;
@@ -90,7 +93,7 @@ struct prism_ctx {
   ActOut xfc;                       // FC operand planes [R, H + feat_max]
   float *u = nullptr, *r1 = nullptr;  // residual stream rows [R, H]
   ActOut ug, r1g, hg;               // (x * gain) operand planes [R, H]
-  ActOut lmr_x;                     // bf16: LM-head operand rows of a tree-scoring pass [LMR_MAX_ROWS, H]
+  ActOut lmr_x;                     // bf16: LM-head operand rows of a tree-scoring pass [LMR_MAX_ROWS, H], tiled
   float *lmr_scale = nullptr;       // and their row scales
   float *ss_u = nullptr, *ss_r1 = nullptr, *ss_h = nullptr;  // [parts <= H/16][R]
   float *sc_u = nullptr, *sc_r1 = nullptr, *sc_h = nullptr;  // row scales [R]
@@ -111,7 +114,8 @@ struct prism_ctx {
   int att_grp = 1;                  // tree levels: rows per attention workgroup
   int lm_nwg_last = 0;              // LM-head partial count of the pass last enqueued
   int new_max = 0;                  // catch-up rows capacity
-  int front_max = 0;                // rows of one catch-up front chunk
+  int front_max = 0;                // rows of one catch-up front chunk through xfc
+  int long_max = 0;                 // rows of one chunk of a long front (read in place)
   int32_t *c_rseq = nullptr, *c_rpos = nullptr, *c_last = nullptr;   // catch-up rows
   // tree scoring: the rows of every tree, [max_batch * (MAX_SCORE_NODES + 1)]
   int32_t *s_tok = nullptr, *s_seq = nullptr, *s_pos = nullptr, *s_slot = nullptr;
@@ -267,14 +271,20 @@ prism_status prism_create(const prism_config *cfg, prism_ctx **out) {
   c->n_wg_lm = lm_workgroups(c->lm.n_tiles, 1);
   if (const char *e = getenv("PRISM_NO_GRAPH")) c->use_graph = !(e[0] == '1');
 
-  // rows of a drafting pass (R), of any pass (RP: tree scoring), and of one
-  // chunk of the fusion FC / QKV front of a catch-up step too (RF: the
-  // accepted tokens, at most MAX_ROWS per chunk)
-  const size_t R = rows, RP = c->pass_max, es = c->esz;
-  const int front_rows = k.max_new_rows < MAX_ROWS ? k.max_new_rows : MAX_ROWS;
-  const size_t RF = (int)RP > front_rows ? RP : front_rows;
+  // rows of a drafting pass (R), of any pass (RP: tree scoring), of one
+  // chunk of the fusion FC / QKV front of a catch-up step through the staged
+  // operand (RX: up to MAX_ROWS accepted tokens, or as many as a pass), and of
+  // one chunk of a long front, which reads the features in place (RF);
+  // operand planes hold whole 16-row tiles
+  const size_t es = c->esz;
+  auto pad16 = [&](int n) { return (size_t)(bf16 ? (n + 15) / 16 * 16 : n); };
+  const size_t R = rows, RP = pad16(c->pass_max);
+  const int front_rows = std::max(c->pass_max, std::min(k.max_new_rows, MAX_ROWS));
   c->new_max = k.max_new_rows;
-  c->front_max = (int)RF;
+  c->front_max = front_rows;
+  c->long_max = c->use_tab ? std::min(k.max_new_rows, ROWGRP_MAX_ROWS) : 0;
+  const size_t RX = pad16(front_rows);
+  const size_t RF = std::max(RX, pad16(c->long_max));
   size_t total = 0;
   std::vector<std::pair<void **, size_t>> L;
   auto add = [&](void **p, size_t b) { L.push_back({p, b}); total += (b + 255) & ~(size_t)255; };
@@ -283,7 +293,7 @@ prism_status prism_create(const prism_config *cfg, prism_ctx **out) {
     if (bf16) add(&a.lo, n * es);
   };
   const size_t nth = (size_t)c->H / 16;
-  planes(c->xfc, RF * (c->H + c->feat_max));
+  planes(c->xfc, RX * (c->H + c->feat_max));
   add((void **)&c->u, RF * c->H * 4);
   add((void **)&c->r1, RP * c->H * 4);
   planes(c->ug, RF * c->H);
@@ -299,7 +309,7 @@ prism_status prism_create(const prism_config *cfg, prism_ctx **out) {
   add((void **)&c->sc_u, RF * 4);
   add((void **)&c->sc_r1, RP * 4);
   add((void **)&c->sc_h, RP * 4);
-  add((void **)&c->q, RF * c->nq * c->d * 4);
+  add((void **)&c->q, RX * c->nq * c->d * 4);
   add((void **)&c->pm, part_rc * c->nq * 4);
   add((void **)&c->pl, part_rc * c->nq * 4);
   add((void **)&c->po, part_rc * c->nq * c->d * 4);
@@ -309,16 +319,18 @@ prism_status prism_create(const prism_config *cfg, prism_ctx **out) {
   add((void **)&c->hid[1], R * c->H * 4);
   if ((int)RF > GEMV_MAX_ROWS) {   // batched products: K-slice partial sums [split][rows][N]
     size_t pn = 0;
-    auto upd = [&](int N, int K) {
+    auto upd = [&](int N, int K, size_t rmax) {
       const TiledMat t = make_tiled(N, K, bf16);
-      pn = std::max(pn, product_partial_floats(t.n_tiles, t.nkb, t.K, (int)RF));
+      pn = std::max(pn, product_partial_floats(t.n_tiles, t.nkb, t.K, (int)rmax));
     };
-    upd(c->H, c->H + k.feat_width);
-    upd(c->H, 2 * c->H);
-    upd(c->QKV, c->H);
-    upd(c->H, c->nq * c->d);
-    upd(2 * c->I, c->H);
-    upd(c->H, c->I);
+    upd(c->H, c->H + k.feat_width, RF);
+    upd(c->H, 2 * c->H, RX);
+    upd(c->QKV, c->H, RX);
+    upd(2 * c->nkv * c->d, c->H, RF);
+    upd(c->nq * c->d, c->H, R);
+    upd(c->H, c->nq * c->d, RX);
+    upd(2 * c->I, c->H, RX);
+    upd(c->H, c->I, RX);
     add((void **)&c->part, pn * 4);
   }
   add((void **)&c->lm_max, R * c->n_wg_lm * 4);
@@ -555,7 +567,15 @@ static Act act_of(const ActOut &o, int ld) {
   a.hi = o.hi;
   a.lo = o.lo;
   a.ld = ld;
+  a.pk = o.pk;
   return a;
+}
+
+// operand planes of a pass over R rows: tiled for the tile kernel
+static ActOut planes_for(const prism_ctx *c, ActOut o, int ld, int R) {
+  o.ld = ld;
+  o.pk = c->bf16 && R > MAX_ROWS;
+  return o;
 }
 
 // RMSNorm row scales for a consumer: reduced by the consumer itself from the
@@ -617,42 +637,141 @@ static void gemm_go(prism_ctx *c, const GemmLaunch &g, hipStream_t s) {
   prof_end(c, pr, s);
 }
 
+// Fusion FC of a tree-scoring pass whose rows share one feature row per tree:
+// the feature columns are multiplied for the R / fc_div trees only, and the
+// finish pass writes every row (its tree's product plus its token's table
+// row).  8B, 4 trees of 61 rows: 52 -> 28 us against 244 rows multiplied.
+static int enqueue_fc_trees(prism_ctx *c, const Pass &p, hipStream_t s) {
+  const Set &S = c->sets[p.set];
+  const int H = c->H, nt = p.R / p.fc_div, kb_lo = H / 32;
+  ActOut X = c->xfc;
+  X.ld = H + p.F;
+  RowsIn in = p.in;
+  in.feat_rows = nullptr;
+  launch_fc_prep(true, nt, in, TokFromLm{}, c->embed, c->V, H, p.F, X, c->err, nullptr, true, s);
+  GemmLaunch g{};
+  g.m = S.fc;
+  g.x = act_of(X, H + p.F);
+  g.R = nt;
+  g.kb_lo = kb_lo;
+  g.part = c->part;
+  plan_batched(g.m.n_tiles, g.m.nkb - kb_lo, p.F, nt, g.nt, g.split);
+  const int pr = prof_begin(c, PRISM_PROFILE_PRODUCTS, s);
+  if (!launch_gemm_slices(g, s)) c->enq_bad = true;
+  g.R = p.R;
+  g.part_div = p.fc_div;
+  g.part_rows = nt;
+  g.epi = EPI_NORM;
+  g.tab = S.tab; g.tab_tok = p.in.tokens; g.tab_V = c->V; g.err = c->err;
+  g.y = c->u; g.ldy = H; g.gain = S.g1; g.g = planes_for(c, c->ug, H, p.R); g.ss = c->ss_u;
+  launch_gemm_finish(g, s);
+  prof_end(c, pr, s);
+  return gemm_ss_parts(g);
+}
+
 // Front of a pass: fusion FC and QKV (RoPE, KV append) for p.R rows -> u
 // and q in the workspace.
 static void enqueue_front(prism_ctx *c, const Pass &p, const KvArgs &kv, hipStream_t s) {
   const Set &S = c->sets[p.set];
   const bool bf = c->bf16;
   const int R = p.R, H = c->H;
-  // fusion FC: u = W_fc [E(x) ; f]  ->  u, (u * g1), sums of squares
-  ActOut X = c->xfc;
-  X.ld = H + p.F;
-  // with the set's embedding table the product covers the feature columns
-  // only, and its epilogue adds the table row of each row's token
-  const int kb_lo = S.tab_ready ? H / (bf ? 32 : 16) : 0;
-  GemmLaunch g = gemm_of(c, S.fc, act_of(X, H + p.F), R, EPI_NORM, kb_lo);
-  if (S.tab_ready) g.tab = S.tab;
-  if (g.gemv) {   // the GEMV stages [E(x) ; f] (or f) itself
-    g.gx.embed = c->embed; g.gx.V = c->V; g.gx.H = H; g.gx.in = p.in; g.gx.lm = p.lm_in;
-    g.err = c->err;
-  } else if (p.op_in) {
-    // the feature columns were written by the previous down product; the
-    // K-split kernel resolves the tokens for its finish pass
-    g.tab_tok = c->tab_tok;
-    g.tok_out = c->tab_tok;
-    g.gx.V = c->V; g.gx.in = p.in; g.gx.lm = p.lm_in;
-    g.err = c->err;
+  const ActOut ug = planes_for(c, c->ug, H, R);
+  int parts_u;
+  GemmLaunch g;
+  if (p.fc_div) {
+    parts_u = enqueue_fc_trees(c, p, s);
   } else {
-    if (S.tab_ready) g.tab_tok = c->tab_tok;
-    launch_fc_prep(bf, R, p.in, p.lm_in, c->embed, c->V, H, p.F, X, c->err,
-                   S.tab_ready ? c->tab_tok : nullptr, S.tab_ready, s);
+    // fusion FC: u = W_fc [E(x) ; f]  ->  u, (u * g1), sums of squares
+    const ActOut X = planes_for(c, c->xfc, H + p.F, R);
+    // with the set's embedding table the product covers the feature columns
+    // only, and its epilogue adds the table row of each row's token
+    const int kb_lo = S.tab_ready ? H / (bf ? 32 : 16) : 0;
+    g = gemm_of(c, S.fc, act_of(X, H + p.F), R, EPI_NORM, kb_lo);
+    if (S.tab_ready) g.tab = S.tab;
+    if (g.gemv) {   // the GEMV stages [E(x) ; f] (or f) itself
+      g.gx.embed = c->embed; g.gx.V = c->V; g.gx.H = H; g.gx.in = p.in; g.gx.lm = p.lm_in;
+      g.err = c->err;
+    } else if (p.op_in) {
+      // the feature columns were written by the previous down product; the
+      // K-split kernel resolves the tokens for its finish pass
+      g.tab_tok = c->tab_tok;
+      g.tok_out = c->tab_tok;
+      g.gx.V = c->V; g.gx.in = p.in; g.gx.lm = p.lm_in;
+      g.err = c->err;
+    } else {
+      if (S.tab_ready) g.tab_tok = c->tab_tok;
+      launch_fc_prep(bf, R, p.in, p.lm_in, c->embed, c->V, H, p.F, X, c->err,
+                     S.tab_ready ? c->tab_tok : nullptr, S.tab_ready, s);
+    }
+    g.y = c->u; g.ldy = H; g.gain = S.g1; g.g = ug; g.ss = c->ss_u;
+    gemm_go(c, g, s);
+    parts_u = gemm_ss_parts(g);
   }
-  g.y = c->u; g.ldy = H; g.gain = S.g1; g.g = c->ug; g.g.ld = H; g.ss = c->ss_u;
-  gemm_go(c, g, s);
-  const int parts_u = gemm_ss_parts(g);
   // q, k, v = W_qkv RMSNorm(u; g1);  RoPE;  k, v -> cache slot
-  g = gemm_of(c, S.qkv, act_of(c->ug, H), R, EPI_QKV);
+  g = gemm_of(c, S.qkv, act_of(ug, H), R, EPI_QKV);
   g.norm = norm_for(c, c->ss_u, parts_u, gemm_own_scales(g, parts_u), c->sc_u, R, s);
   g.q = c->q; g.nq = c->nq; g.nkv = c->nkv; g.d = c->d;
+  g.rows = p.in; g.kv = kv; g.inv_freq = c->inv_freq; g.err = c->err;
+  gemm_go(c, g, s);
+}
+
+// the q (or the k and v) rows of a set's QKV product
+static TiledMat qkv_part(const prism_ctx *c, const TiledMat &m, bool q, int &tile0) {
+  const int qt = c->nq * c->d / 16;
+  TiledMat t = m;
+  tile0 = q ? 0 : qt;
+  t.n_tiles = q ? qt : m.n_tiles - qt;
+  t.N = 16 * t.n_tiles;
+  t.w = (char *)m.w + (size_t)tile0 * m.nkb * 1024;
+  return t;
+}
+
+// Front of a long catch-up (more than MAX_ROWS accepted rows, bf16, table
+// ready, features 16-byte aligned): the rows before a sequence's last only
+// leave their k and v in the cache, so the FC runs over every row (reading
+// the target features in place: one exact bf16 plane), the k and v rows of
+// the QKV product over every row, and its q rows over the B last rows.
+// q and u of the last rows go to q2 and u2.  8B, one prompt of 1531 tokens:
+// the front 864 -> 340 us against 256-row chunks of the whole QKV product
+// with a staged hi/lo operand.
+static void enqueue_long_front(prism_ctx *c, const Pass &p, const prism_catchup &cu, int B,
+                               const KvArgs &kv, hipStream_t s) {
+  const Set &S = c->sets[p.set];
+  const int H = c->H, F = p.F, T = cu.total_rows;
+  const int chunks = (T + c->long_max - 1) / c->long_max;
+  for (int i = 0; i < chunks; ++i) {
+    const int r0 = (int)((long)i * T / chunks), n = (int)((long)(i + 1) * T / chunks) - r0;
+    RowsIn in{};
+    in.tokens = cu.d_tokens + r0;
+    in.seq = c->c_rseq + r0;
+    in.pos = in.slot = c->c_rpos + r0;
+    Act X;
+    X.hi = (const bf16_t *)cu.d_features + (size_t)r0 * F;
+    X.ld = F;
+    GemmLaunch g = gemm_of(c, S.fc, X, n, EPI_NORM, H / 32);
+    g.tab = S.tab; g.tab_tok = in.tokens; g.tab_V = c->V; g.err = c->err;
+    g.y = c->u; g.ldy = H; g.gain = S.g1; g.g = planes_for(c, c->ug, H, n); g.ss = c->ss_u;
+    gemm_go(c, g, s);
+    const int parts_u = gemm_ss_parts(g);
+    int tile0;
+    const TiledMat kvm = qkv_part(c, S.qkv, false, tile0);
+    const ActOut ug = g.g;
+    g = gemm_of(c, kvm, act_of(ug, H), n, EPI_QKV);
+    g.tile0 = tile0;
+    g.norm = norm_for(c, c->ss_u, parts_u, gemm_own_scales(g, parts_u), c->sc_u, n, s);
+    g.q = c->q; g.nq = c->nq; g.nkv = c->nkv; g.d = c->d;
+    g.rows = in; g.kv = kv; g.inv_freq = c->inv_freq; g.err = c->err;
+    gemm_go(c, g, s);
+    LastRows lr{};
+    lr.idx = c->c_last; lr.r0 = r0; lr.n_src = n; lr.H = H; lr.eps = c->cfg.rms_eps;
+    lr.u = c->u; lr.gain = S.g1; lr.dst = c->u2; lr.x = planes_for(c, c->r1g, H, B); lr.scale = c->sc_r1;
+    launch_last_rows(B, lr, s);
+  }
+  int tile0;
+  const TiledMat qm = qkv_part(c, S.qkv, true, tile0);
+  GemmLaunch g = gemm_of(c, qm, act_of(planes_for(c, c->r1g, H, B), H), B, EPI_QKV);
+  g.norm.scale = c->sc_r1;
+  g.q = c->q2; g.nq = c->nq; g.nkv = c->nkv; g.d = c->d;
   g.rows = p.in; g.kv = kv; g.inv_freq = c->inv_freq; g.err = c->err;
   gemm_go(c, g, s);
 }
@@ -665,23 +784,23 @@ static void enqueue_back(prism_ctx *c, const Pass &p, const KvArgs &kv, const fl
   const bool bf = c->bf16;
   const int R = p.R, H = c->H;
   // attention over the visible slots -> o
-  ActOut o = c->o;
-  o.ld = c->nq * c->d;
+  const ActOut o = planes_for(c, c->o, c->nq * c->d, R);
   launch_attention(bf, R, c->nq, c->nkv, c->d, q, p.in, kv, c->max_slots, p.grp, p.rps, c->pm, c->pl,
                    c->po, o, c->err, s);
   // r1 = u + W_o o  ->  r1, (r1 * g2), sums of squares
   GemmLaunch g = gemm_of(c, S.o, act_of(o, c->nq * c->d), R, EPI_NORM);
-  g.res = u; g.ldres = H; g.y = c->r1; g.ldy = H; g.gain = S.g2; g.g = c->r1g; g.g.ld = H;
+  g.res = u; g.ldres = H; g.y = c->r1; g.ldy = H; g.gain = S.g2;
+  g.g = planes_for(c, c->r1g, H, R);
   g.ss = c->ss_r1;
   gemm_go(c, g, s);
   const int parts_r1 = gemm_ss_parts(g);
   // z = SiLU(W_gate m) * (W_up m),  m = RMSNorm(r1; g2)
-  g = gemm_of(c, S.gu, act_of(c->r1g, H), R, EPI_SWIGLU);
+  g = gemm_of(c, S.gu, act_of(g.g, H), R, EPI_SWIGLU);
   g.norm = norm_for(c, c->ss_r1, parts_r1, gemm_own_scales(g, parts_r1), c->sc_r1, R, s);
-  g.z = c->z; g.z.ld = c->I;
+  g.z = planes_for(c, c->z, c->I, R);
   gemm_go(c, g, s);
   // h = r1 + W_down z  ->  h (output), (h * g_final), sums of squares
-  g = gemm_of(c, S.down, act_of(c->z, c->I), R, EPI_NORM);
+  g = gemm_of(c, S.down, act_of(g.z, c->I), R, EPI_NORM);
   g.res = c->r1; g.ldres = H; g.y = p.hid_out; g.ldy = p.ld_hid; g.gain = c->gf;
   g.g = p.lm_rows_x.hi ? p.lm_rows_x : c->hg;
   g.g.ld = H; g.ss = c->ss_h;
@@ -969,13 +1088,18 @@ static void enqueue_chain(prism_ctx *c, const prism_batch &b, const KvArgs &kv, 
     p.ld_b = K;
     if (k == 1 && cu) {
       const int pr = prof_begin(c, PRISM_PROFILE_PASSES, s);
+      // a long front reads the features in place (16-byte loads of rows of
+      // feat_width, a multiple of 32); others run as follows
+      const bool in_place = cu->total_rows > MAX_ROWS && c->long_max > 0 &&
+                            c->sets[p.set].tab_ready && ((uintptr_t)cu->d_features & 15) == 0;
+      if (in_place) enqueue_long_front(c, p, *cu, B, kv, s);
       // front over every accepted row, in chunks of at most front_max rows:
       // the front (FC, QKV, KV append) of one row depends on no other row,
       // and only each sequence's last row runs the attention, after every
       // chunk has written its KV; that row's q and u are kept as its chunk
       // passes
       const size_t fb = (size_t)c->cfg.feat_width * c->esz;
-      for (int r0 = 0; r0 < cu->total_rows; r0 += c->front_max) {
+      for (int r0 = 0; !in_place && r0 < cu->total_rows; r0 += c->front_max) {
         const int n = cu->total_rows - r0 < c->front_max ? cu->total_rows - r0 : c->front_max;
         Pass f = p;
         f.R = n;
@@ -1239,12 +1363,11 @@ prism_status prism_score_tree(prism_ctx *c, const prism_batch *batch, int32_t n_
                                 (uintptr_t)d_logits, (uintptr_t)c->fmap[0]};
   const int set = c->fmap[0];
   const int rps = n_nodes + 1;   // each tree's rows: its root, then its nodes
-  // bf16: passes of whole trees, up to pass_max rows (the row-group
+  // bf16: passes of whole trees, up to pass_max rows (the tile kernel's
   // products), the tree's rows grouped in the attention, and one LM head over
   // each pass's rows; otherwise passes of up to rows_max rows with their own
   // LM heads
-  const bool wide = c->bf16 && c->pass_max > c->rows_max && c->lmr_x.hi &&
-                    lmhead_rows_fits(c->lm, c->pass_max) && rps <= c->pass_max;
+  const bool wide = c->bf16 && c->pass_max > c->rows_max && c->lmr_x.hi && rps <= c->pass_max;
   const int per_pass = wide ? c->pass_max / rps * rps : c->rows_max;
   return run_graph(c, key, (hipStream_t)stream, [&](hipStream_t s) {
     launch_score_setup(B, n_nodes, b.d_tokens, b.d_ctx_lens, d_tokens, d_depth, d_mask, c->s_tok,
@@ -1278,13 +1401,18 @@ prism_status prism_score_tree(prism_ctx *c, const prism_batch *batch, int32_t n_
         p.rps = rps;
         p.lm_rows_x = c->lmr_x;
         p.lm_rows_x.ld = c->H;
+        p.lm_rows_x.pk = 1;
+        if (c->sets[set].tab_ready && n / rps <= MAX_ROWS) {   // one feature row per tree
+          p.fc_div = rps;
+          p.in.feat = (const char *)b.d_features + (size_t)(r0 / rps) * p.F * c->esz;
+        }
         p.lm_rows_scale = c->lmr_scale;
       }
       enqueue_pass(c, p, kv, s);
       if (wide) {   // the pass's LM head
         LmRowsArgs a{};
         a.m = c->lm;
-        a.x = act_of(c->lmr_x, c->H);
+        a.x = act_of(p.lm_rows_x, c->H);
         a.R = n;
         a.scale = c->lmr_scale;
         a.logits = d_logits + (size_t)r0 * V;

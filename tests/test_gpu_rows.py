@@ -1,0 +1,98 @@
+"""Passes of more rows than the 16-row-tile kernels take (bf16): the tile
+kernel at the edges of its row and feature tiles, and the two routes that
+read feature rows once instead of per row, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from harness import LOGIT_TOL, check_chain, check_draft_kv, gpu_setup, log, oracle_for
+from synth import SMALL_BF16_CHAIN, host_inputs, host_weights, make_inputs, make_weights, scoring_target
+
+pytestmark = pytest.mark.gpu
+
+
+# accepted rows in all: one past the small kernels, whole and one past a
+# 64- and a 128-row tile, two chunks of a long front; hidden 480: no
+# embedding table, so the staged operand and the whole QKV product
+@pytest.mark.parametrize("batch,n,hidden", [(1, 65, 512), (2, 64, 512), (3, 43, 512), (1, 193, 512),
+                                            (1, 2049, 512), (1, 129, 480), (5, 53, 480)])
+def test_catchup_row_tiles(batch, n, hidden):
+    cfg = SMALL_BF16_CHAIN.with_(name="small_catchup_%dx%d_h%d" % (batch, n, hidden), batch=batch,
+                                 n_new=(n, n), ctx_range=(0, 40), n_steps=2, hidden=hidden)
+    dr, w, inp = gpu_setup(cfg)
+    out = dr.chain_catchup(inp, logits=True, hidden=True)
+    torch.cuda.synchronize()
+    assert dr.device_status() == 0
+    seqs = [0, batch - 1] if batch > 1 else [0]
+    orc, hi = oracle_for(cfg, w, inp, seqs)
+    log(cfg.name, check_chain(cfg, out, orc, hi, seqs, catchup=True, inp=inp))
+    dr.close()
+
+
+def test_catchup_features_at_any_address():
+    """Features that are not 16-byte aligned take the staged operand, and give
+    what the route that reads them in place gives (both against the oracle)."""
+    cfg = SMALL_BF16_CHAIN.with_(name="small_catchup_unaligned", batch=2, n_new=(50, 70), n_steps=2)
+    dr, w, inp = gpu_setup(cfg)
+    orc, hi = oracle_for(cfg, w, inp, [0, 1])
+    flat = torch.zeros(inp.new_features.numel() + 8, dtype=torch.bfloat16, device="cuda")
+    for shift in (0, 1, 4):
+        view = flat[shift:shift + inp.new_features.numel()].view_as(inp.new_features)
+        view.copy_(inp.new_features)
+        assert (view.data_ptr() % 16 == 0) == (shift == 0)
+        x = type(inp)(**{**inp.__dict__, "new_features": view})
+        out = dr.chain_catchup(x, logits=True, hidden=True)
+        torch.cuda.synchronize()
+        assert dr.device_status() == 0
+        check_chain(cfg, out, orc, hi, [0, 1], catchup=True, inp=inp)
+    dr.close()
+
+
+def test_long_catchup_flags_bad_tokens():
+    cfg = SMALL_BF16_CHAIN.with_(name="small_catchup_badtok", batch=1, n_new=(80, 80), n_steps=1)
+    dr, w, inp = gpu_setup(cfg)
+    good = inp.new_tokens.clone()
+    inp.new_tokens[7] = cfg.vocab
+    dr.chain_catchup(inp)
+    assert dr.device_status() == -1
+    inp.new_tokens.copy_(good)
+    dr.chain_catchup(inp)
+    assert dr.device_status() == 0
+    dr.close()
+
+
+# trees x (nodes + 1) rows: one tree below the small kernels' limit, whole
+# row tiles, one row past a tile, passes of whole trees; 1 node: 2 rows share
+# a feature row; hidden 480: no embedding table
+@pytest.mark.parametrize("batch,nodes,hidden", [(1, 60, 512), (2, 63, 512), (3, 42, 512), (1, 1, 512),
+                                                (64, 1, 512), (9, 28, 512), (3, 42, 480)])
+def test_score_rows_share_their_trees_features(batch, nodes, hidden):
+    """Scoring with target features that are not zero: every row of a tree
+    fuses its sequence's feature row."""
+    from oracle import Oracle
+    from paper_2602_01762_amd import Drafter
+    cfg = scoring_target(SMALL_BF16_CHAIN.with_(
+        name="small_score_%dx%d" % (batch, nodes), batch=batch, tree_nodes=nodes, tree_width=1,
+        hidden=hidden, ctx_range=(3, 90)))
+    w, inp = make_weights(cfg, "cuda"), make_inputs(cfg, "cuda")
+    dr = Drafter(cfg)
+    dr.load(w)
+    rng = np.random.default_rng(batch * 100 + nodes)
+    depth = np.ones((batch, nodes), np.int32)
+    mask = np.zeros((batch, nodes), np.uint64)
+    for b in range(batch):
+        for j in range(nodes):
+            p = int(rng.integers(-1, j)) if j else -1
+            depth[b, j] = 1 if p < 0 else depth[b, p] + 1
+            mask[b, j] = (np.uint64(0) if p < 0 else mask[b, p]) | (np.uint64(1) << np.uint64(j))
+    toks = rng.integers(0, cfg.vocab, (batch, nodes)).astype(np.int32)
+    dev = lambda x: torch.tensor(x, device="cuda")
+    lg = dr.score_tree(inp, dev(toks), dev(depth), dev(mask.view(np.int64)))
+    torch.cuda.synchronize()
+    assert dr.device_status() == 0
+    seqs = sorted({0, batch // 2, batch - 1})
+    ref = Oracle(cfg, host_weights(w)).score_tree(host_inputs(inp, cfg, seqs), toks, depth, mask, seqs)
+    for b in seqs:
+        assert np.max(np.abs(lg[b].cpu().numpy() - ref["logits"][b])) <= LOGIT_TOL["bf16"], b
+    check_draft_kv(cfg, inp, ref["draft_kv"], seqs)
+    dr.close()
