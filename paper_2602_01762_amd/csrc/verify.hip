@@ -7,12 +7,14 @@
 // longest root path whose every node is the target's choice at its parent.
 //
 // Logits rows are V-wide fp32 (0.5 MB at V = 128256), so the work is a
-// stream over them: k_rows_stats splits each row over VSPLIT workgroups,
-// each reducing its slice to (max z, sum exp(z - max), arg-max of the raw
-// logits), z = logit / T (greedy verification: the arg-max only); one
-// workgroup per sequence then merges the slices in order and takes the
-// decisions.  Draws use the drafter's inverse CDF
-// in token-id order.
+// stream over them, bound by HBM: each row is split over several workgroups,
+// which reduce their slices to (max z, sum exp(z - max)), z = logit / T
+// (sampled), or to the arg-max (greedy).  A sampled call then decides per
+// sequence and sums the weights of the one row it draws from, again a slice
+// per workgroup, and one workgroup per sequence walks the slice that holds
+// the draw: 8B vocabulary, batch 16, K 5 (90 MB), 75.7 -> 34.3 us per call
+// (one workgroup per sequence summing and walking its whole row took 39 us
+// alone).  Draws use the drafter's inverse CDF in token-id order.
 #include <cstdarg>
 #include <cstdio>
 #include <mutex>
@@ -22,138 +24,279 @@
 
 namespace prism {
 
-constexpr int VSPLIT = 8;
+constexpr int VSPLIT = 8;        // slices per row at least
+constexpr int VSPLIT_MAX = 32;   // and at most (8, 16 or 32)
+constexpr int VSPLIT_WGS = 1024; // as long as the slices of all rows stay within this many
 constexpr int VER_UNROLL = 4;
 
-struct RowStat {      // one slice of one row
-  float mx, sum, best;
+// Slices per row of a call over `rows` rows: 8 (16032 ids of the 8B
+// vocabulary, four batches of 16-byte loads per thread) once that fills the
+// chip, more for few rows, where the call is the latency of one slice.
+static int row_slices(int rows) {
+  int n = VSPLIT;
+  while (n < VSPLIT_MAX && rows * n * 2 <= VSPLIT_WGS) n *= 2;
+  return n;
+}
+
+struct SoftStat {     // one slice of one row: softmax statistics of z = logit / T
+  float mx, sum;
+};
+struct BestStat {     // arg-max (the lowest id if several)
+  float best;
   int arg;
 };
 
-// slice of a row: ids [lo, hi) with lo a multiple of 4 (16-byte loads)
-__device__ __forceinline__ void slice_of(int V, int part, int &lo, int &hi) {
-  const int per = (((V + VSPLIT - 1) / VSPLIT) + 3) & ~3;
+// slice of a row: ids [lo, hi), both multiples of 4 (V is a multiple of 16)
+__device__ __forceinline__ void slice_of(int V, int part, int parts, int &lo, int &hi) {
+  const int per = (((V + parts - 1) / parts) + 3) & ~3;
   lo = min(V, part * per);
   hi = min(V, lo + per);
 }
 
-// SOFT = false (greedy verification, which reads only the arg-max): no
-// exponentials, and the statistics stored as (-inf, 0).
-template <bool SOFT>
-__global__ __launch_bounds__(256) void k_rows_stats(const float *__restrict__ x, int V,
-                                                    float inv_t, RowStat *out) {
+// Softmax statistics of rows0 rows of x0, then of the rows of x1.  A thread
+// keeps a running (max, sum) and takes 16 values at a time: one rescale per
+// batch and one exponential per value.  (Rescaling value by value, with both
+// sides of the branch run, cost two: 19 us for 49 MB.)
+__global__ __launch_bounds__(256) void k_rows_soft(const float *__restrict__ x0, int rows0,
+                                                   const float *__restrict__ x1, int V, float inv_t,
+                                                   SoftStat *out) {
+  __shared__ float sh[8];
+  const int row = blockIdx.y, part = blockIdx.x, parts = gridDim.x, tid = threadIdx.x;
+  int lo, hi;
+  slice_of(V, part, parts, lo, hi);
+  const float *r = row < rows0 ? x0 + (size_t)row * V : x1 + (size_t)(row - rows0) * V;
+  float m = -INFINITY, s = 0.f;
+  for (int i0 = lo + 4 * tid; i0 < hi; i0 += 4 * 256 * VER_UNROLL) {
+    f32x4 v[VER_UNROLL];
+#pragma unroll
+    for (int u = 0; u < VER_UNROLL; ++u) {
+      const int i = i0 + u * 4 * 256;
+      v[u] = *(const f32x4 *)(r + (i < hi ? i : i0));
+      if (i >= hi) v[u] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    }
+    float mn = m;
+#pragma unroll
+    for (int u = 0; u < VER_UNROLL; ++u) {
+      v[u] *= inv_t;
+      mn = fmaxf(mn, fmaxf(fmaxf(v[u].x, v[u].y), fmaxf(v[u].z, v[u].w)));
+    }
+    const float ref = mn == -INFINITY ? 0.f : mn;   // only -inf so far: every term is 0
+    s *= expf(m - ref);
+#pragma unroll
+    for (int u = 0; u < VER_UNROLL; ++u)
+      s += (expf(v[u].x - ref) + expf(v[u].y - ref)) + (expf(v[u].z - ref) + expf(v[u].w - ref));
+    m = mn;
+  }
+  const float M = block_max(m, sh);
+  const float S = block_sum(m == -INFINITY ? 0.f : s * expf(m - M), sh);
+  if (tid == 0) out[(size_t)row * parts + part] = SoftStat{M, S};
+}
+
+// Arg-max of each row's slice.  A thread's ids ascend, so a strictly larger
+// value is taken; a thread that saw none above -inf looks for its first -inf.
+__global__ __launch_bounds__(256) void k_rows_best(const float *__restrict__ x, int V, BestStat *out) {
   __shared__ float shv[8];
   __shared__ int shi[8];
-  const int row = blockIdx.y, part = blockIdx.x, tid = threadIdx.x;
+  const int row = blockIdx.y, part = blockIdx.x, parts = gridDim.x, tid = threadIdx.x;
   int lo, hi;
-  slice_of(V, part, lo, hi);
-  const float *r = x + (size_t)row * V;   // V % 4 == 0: rows are 16-byte aligned
-  float mz = -INFINITY, s = 0.f, bv = -INFINITY;
-  int bi = 0x7fffffff;
-  auto take = [&](float v, int i) {
-    if (better(v, i, bv, bi)) { bv = v; bi = i; }
-    if (!SOFT) return;
-    const float z = v * inv_t;            // online max / sum of exp(z - max)
-    if (z > mz) {
-      s = s * expf(mz - z) + 1.f;
-      mz = z;
-    } else {
-      s += expf(z - mz);
-    }
-  };
+  slice_of(V, part, parts, lo, hi);
+  const float *r = x + (size_t)row * V;
+  float bv = -INFINITY;
+  int bi = NO_TOKEN;
   for (int i0 = lo + 4 * tid; i0 < hi; i0 += 4 * 256 * VER_UNROLL) {
     f32x4 v[VER_UNROLL];
 #pragma unroll
     for (int u = 0; u < VER_UNROLL; ++u) {   // all loads first
       const int i = i0 + u * 4 * 256;
-      v[u] = i + 3 < hi ? *(const f32x4 *)(r + i) : f32x4{0.f, 0.f, 0.f, 0.f};
-      if (i < hi && i + 3 >= hi)
-        for (int q = 0; q < 4; ++q) v[u][q] = i + q < hi ? r[i + q] : 0.f;
+      v[u] = *(const f32x4 *)(r + (i < hi ? i : i0));   // past the end: i0 again, never larger
     }
 #pragma unroll
     for (int u = 0; u < VER_UNROLL; ++u) {
       const int i = i0 + u * 4 * 256;
-      for (int q = 0; q < 4; ++q)
-        if (i + q < hi) take(v[u][q], i + q);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool take = v[u][q] > bv;
+        bv = take ? v[u][q] : bv;
+        bi = take ? i + q : bi;
+      }
     }
   }
-  float M = -INFINITY, S = 0.f;
-  if constexpr (SOFT) {
-    M = block_max(mz, shv);
-    S = block_sum(mz == -INFINITY ? 0.f : s * expf(mz - M), shv);
-  }
+  if (bi == NO_TOKEN)
+    for (int i0 = lo + 4 * tid; i0 < hi && bi == NO_TOKEN; i0 += 4 * 256)
+      for (int q = 3; q >= 0; --q)
+        if (r[i0 + q] == -INFINITY) bi = i0 + q;
   block_argmax(bv, bi, shv, shi);
-  if (tid == 0) out[(size_t)row * VSPLIT + part] = RowStat{M, S, bv, bi};
+  if (tid == 0) out[(size_t)row * parts + part] = BestStat{bv, bi};
 }
 
-// merge the slices of one row: max z, sum exp(z - max), arg-max
+// merges of one row's slices, in slice order
 struct RowSum {
   float M, S;
-  int arg;
 };
-__device__ __forceinline__ RowSum merge_row(const RowStat *st) {
-  float M = -INFINITY, bv = -INFINITY;
-  int bi = 0x7fffffff;
-  for (int p = 0; p < VSPLIT; ++p) {
-    M = fmaxf(M, st[p].mx);
-    if (better(st[p].best, st[p].arg, bv, bi)) { bv = st[p].best; bi = st[p].arg; }
+template <int P>
+__device__ __forceinline__ RowSum merge_soft_n(const SoftStat *st) {
+  SoftStat v[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) v[p] = st[p];   // all loads first
+  float M = -INFINITY, S = 0.f;
+#pragma unroll
+  for (int p = 0; p < P; ++p) M = fmaxf(M, v[p].mx);
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    if (v[p].mx != -INFINITY) S += v[p].sum * expf(v[p].mx - M);
+  return RowSum{M, S};
+}
+__device__ __forceinline__ RowSum merge_soft(const SoftStat *st, int parts) {   // row_slices
+  if (parts == VSPLIT) return merge_soft_n<VSPLIT>(st);
+  if (parts == 2 * VSPLIT) return merge_soft_n<2 * VSPLIT>(st);
+  return merge_soft_n<VSPLIT_MAX>(st);
+}
+__device__ __forceinline__ int merge_best(const BestStat *st, int parts) {
+  float bv = -INFINITY;
+  int bi = NO_TOKEN;
+#pragma unroll 8
+  for (int p = 0; p < parts; ++p) {
+    const BestStat v = st[p];
+    if (better(v.best, v.arg, bv, bi)) { bv = v.best; bi = v.arg; }
   }
-  float S = 0.f;
-  for (int p = 0; p < VSPLIT; ++p)
-    if (st[p].mx != -INFINITY) S += st[p].sum * expf(st[p].mx - M);
-  return RowSum{M, S, bi};
+  return bi;
 }
 
-// Block-wide inverse-CDF draw over ids 0..V-1 with weights w(i) >= 0 (id
-// order).  Ids go in blocks of 256 (lane l of a wave holds ids 4l..4l+3 of a
-// block, one 16-byte load per row); wave w owns a contiguous run of blocks.
-// Pass 1 sums each wave's run; an in-order prefix over the waves finds the
-// run holding u * total.  Pass 2 splits that run over the waves again (a
-// share of a few blocks each, all loaded at once), and a second in-order
-// prefix finds the share; pass 3 walks the share block by block with a lane
-// prefix sum (lane order = id order) to the id.  (One wave walking the whole
-// run waited on one block's load after another.)  Rounding that leaves no
-// crossing takes the highest id of positive weight of the run.  L(base)
-// loads the raw values of ids base..base+3 (unconditionally) and
-// W(raw, base, v[4]) gives their 4 weights (ids >= V weigh 0); the passes
-// load a batch of DRAW_BATCH blocks before weighing them, so that the loads
-// are in flight together.  s_wave holds DRAW_SHARED floats, s_pick 3 ints.
-constexpr int DRAW_THREADS = 1024;
-constexpr int DRAW_WAVES = DRAW_THREADS / 64;
-constexpr int DRAW_SHARED = 2 * DRAW_WAVES + 4;
-constexpr int DRAW_BATCH = 8;
-struct DrawRaw {
-  f32x4 x, y;          // the target row's values (and the draft row's, for the residual)
+constexpr int VER_MAXK = 64;      // drafts per sequence (max_steps <= 63)
+constexpr int DRAW_SLICES = 32;   // slices of the row a sequence draws from
+
+// What a sequence draws from, left by its decision: the target row n, alone
+// (mode 0) or less the draft row (mode 1, the residual at a rejection), their
+// softmax statistics, and the weight of each slice in id order.
+struct Draw {
+  int n, mode;
+  RowSum t, d;
+  float sum[DRAW_SLICES];
 };
 
-// sum of the weights of blocks [b0, b1) in this lane's columns, loaded a
-// batch at a time
-template <typename L, typename W>
-__device__ __forceinline__ float lane_sum(int b0, int b1, int lane, L ld, W wg) {
+struct VerifyChainArgs {
+  int K, V, parts;
+  float inv_t;                   // 0: greedy
+  const float *tl, *dl;          // [B, K+1, V], [B, K, V]
+  const SoftStat *ts, *ds;       // sampled: [B*(K+1)][parts], [B*K][parts]
+  const BestStat *best;          // greedy: [B*(K+1)][parts]
+  Draw *draw;                    // sampled: [B]
+  const int32_t *drafts;         // [B, K]
+  const float *u;                // [B, K+1]
+  int32_t *n_acc, *next;         // [B]
+  uint32_t *err;
+};
+
+// Weights of ids i..i+3 of a sequence's draw (0 past the row): p_target up to
+// its normaliser, or max(0, p_target - p_draft).
+__device__ __forceinline__ f32x4 draw_weights(const Draw &w, int mode, const f32x4 &t, const f32x4 &d,
+                                              float it) {
+  f32x4 v;
+  if (mode == 1) {
+    const float ist = 1.f / w.t.S, isd = 1.f / w.d.S;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      v[q] = fmaxf(0.f, expf(t[q] * it - w.t.M) * ist - expf(d[q] * it - w.d.M) * isd);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = expf(t[q] * it - w.t.M);
+  }
+  return v;
+}
+
+// this thread's share of the weights of ids [lo, hi), the loads of a batch
+// issued together
+__device__ __forceinline__ float slice_weight(const VerifyChainArgs &a, const Draw &w, int mode,
+                                              const float *trow, const float *drow, int lo, int hi) {
   float acc = 0.f;
-  for (int blk = b0; blk < b1; blk += DRAW_BATCH) {
-    DrawRaw raw[DRAW_BATCH];
+  for (int i0 = lo + 4 * (int)threadIdx.x; i0 < hi; i0 += 4 * 256 * VER_UNROLL) {
+    f32x4 t[VER_UNROLL], d[VER_UNROLL];
 #pragma unroll
-    for (int j = 0; j < DRAW_BATCH; ++j) raw[j] = ld(min(blk + j, b1 - 1) * 256 + 4 * lane);
+    for (int u = 0; u < VER_UNROLL; ++u) {
+      const int i = i0 + u * 4 * 256;
+      t[u] = *(const f32x4 *)(trow + (i < hi ? i : i0));
+      d[u] = mode == 1 ? *(const f32x4 *)(drow + (i < hi ? i : i0)) : t[u];
+    }
 #pragma unroll
-    for (int j = 0; j < DRAW_BATCH; ++j) {
-      if (blk + j >= b1) break;
-      float v[4];
-      wg(raw[j], (blk + j) * 256 + 4 * lane, v);
-      acc += (v[0] + v[1]) + (v[2] + v[3]);
+    for (int u = 0; u < VER_UNROLL; ++u) {
+      if (i0 + u * 4 * 256 >= hi) continue;
+      const f32x4 v = draw_weights(w, mode, t[u], d[u], a.inv_t);
+      acc += (v.x + v.y) + (v.z + v.w);
     }
   }
   return acc;
 }
 
-// the first of n in-order sums that carries the running total (from base)
-// past goal: its index and the total before it; none (rounding): the last
-// positive one, with the goal moved to +inf
-__device__ __forceinline__ void pick_in_order(const float *sums, int n, float base, float goal,
-                                              int &pick, float &at, float &g) {
-  float run = base;
+// One workgroup per (slice, sequence): the sequence's decision (every
+// workgroup takes it from the row statistics), and the weight of its slice
+// of the row drawn from.
+__global__ __launch_bounds__(256) void k_verify_decide(VerifyChainArgs a) {
+  __shared__ Draw w;
+  __shared__ RowSum s_t[VER_MAXK + 1], s_d[VER_MAXK];
+  __shared__ float sh[8];
+  const int b = blockIdx.y, part = blockIdx.x, tid = threadIdx.x;
+  const int K = a.K, V = a.V;
+  // lane i of wave 0: draft i and its rows; wave 1: the target rows' statistics
+  float lt = 0.f, ld = 0.f, r = 0.f;
+  int x = -1;
+  if (tid < K) {
+    x = a.drafts[(size_t)b * K + tid];
+    r = a.u[(size_t)b * (K + 1) + tid];
+    if (x < 0 || x >= V) x = -1;
+    if (x < 0 && part == 0) atomicOr(a.err, ERRF_TOKEN);
+    if (x >= 0) {
+      lt = a.tl[((size_t)b * (K + 1) + tid) * V + x];
+      ld = a.dl[((size_t)b * K + tid) * V + x];
+    }
+    s_d[tid] = merge_soft(a.ds + ((size_t)b * K + tid) * a.parts, a.parts);
+  } else if (tid >= 64 && tid - 64 <= K) {
+    s_t[tid - 64] = merge_soft(a.ts + ((size_t)b * (K + 1) + tid - 64) * a.parts, a.parts);
+  }
+  __syncthreads();
+  if (tid < 64) {   // K <= 63: the first draft not kept is one ballot
+    bool stop = tid >= K;
+    if (tid < K && x >= 0) {
+      const float pt = expf(lt * a.inv_t - s_t[tid].M) / s_t[tid].S;
+      const float pd = expf(ld * a.inv_t - s_d[tid].M) / s_d[tid].S;
+      stop = !(r < fminf(1.f, pt / pd));
+    } else if (tid < K) {
+      stop = true;   // an invalid draft is never kept
+    }
+    const int n = __ffsll((long long)__ballot(stop)) - 1;   // lane K always stops
+    const int xn = __shfl(x, n, 64);
+    if (tid == 0) {
+      w.n = n;
+      w.mode = n < K && xn >= 0 ? 1 : 0;
+      w.t = s_t[n];
+      w.d = n < K ? s_d[n] : s_t[n];
+    }
+  }
+  __syncthreads();
+  const float *trow = a.tl + ((size_t)b * (K + 1) + w.n) * V;
+  const float *drow = w.mode == 1 ? a.dl + ((size_t)b * K + w.n) * V : trow;
+  int lo, hi;
+  slice_of(V, part, DRAW_SLICES, lo, hi);
+  const float sum = block_sum(slice_weight(a, w, w.mode, trow, drow, lo, hi), sh);
+  if (tid == 0) {
+    Draw *o = a.draw + b;
+    o->sum[part] = sum;
+    if (part == 0) {
+      o->n = w.n;
+      o->mode = w.mode;
+      o->t = w.t;
+      o->d = w.d;
+    }
+  }
+}
+
+// the first of n in-order sums that carries the running total past goal: its
+// index and the total before it; none (rounding): the last positive one, with
+// the goal moved to +inf
+__device__ __forceinline__ void pick_in_order(const float *sums, int n, float goal, int &pick, float &at,
+                                              float &g) {
+  float run = 0.f;
   pick = -1;
-  at = base;
+  at = 0.f;
   g = goal;
   for (int i = 0; i < n; ++i) {
     if (sums[i] > 0.f && run + sums[i] > goal) { pick = i; at = run; return; }
@@ -164,201 +307,134 @@ __device__ __forceinline__ void pick_in_order(const float *sums, int n, float ba
   g = INFINITY;
 }
 
-template <typename L, typename W>
-__device__ int draw_ids(int V, float u, L ld, W wg, float *s_wave, int *s_pick) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int nblk = (V + 255) / 256;
-  {   // pass 1: each wave's run
-    const int r0 = (int)((long)wave * nblk / DRAW_WAVES), r1 = (int)((long)(wave + 1) * nblk / DRAW_WAVES);
-    const float acc = wave_sum(r1 > r0 ? lane_sum(r0, r1, lane, ld, wg) : 0.f);
-    if (lane == 0) s_wave[wave] = acc;
-  }
+// One workgroup per sequence: the slice that holds u * total, then inside it
+// 4096 ids at a time (16 consecutive ones per thread) an in-order prefix over
+// the threads, and the thread that holds the goal walks its 16.  Rounding
+// that leaves no crossing takes the highest id of positive weight of the
+// slice.  A residual of no weight (identical distributions) draws from the
+// target row instead.
+__global__ __launch_bounds__(256) void k_verify_draw(VerifyChainArgs a) {
+  __shared__ Draw w;
+  __shared__ float sh[8], s_wave[4];
+  __shared__ int s_found, s_last, s_pick;
+  __shared__ float s_at, s_goal;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int K = a.K, V = a.V;
+  for (int i = tid; i < (int)(sizeof(Draw) / 4); i += 256) ((int *)&w)[i] = ((const int *)(a.draw + b))[i];
+  const float u = fminf(fmaxf(a.u[(size_t)b * (K + 1) + K], 0.f), 1.f);
   __syncthreads();
-  if (tid == 0) {
-    float total = 0.f;
-    for (int i = 0; i < DRAW_WAVES; ++i) total += s_wave[i];
-    int pick;
-    float at, g;
-    pick_in_order(s_wave, DRAW_WAVES, 0.f, fminf(fmaxf(u, 0.f), 1.f) * total, pick, at, g);
-    s_pick[0] = pick;
-    s_wave[2 * DRAW_WAVES] = at;
-    s_wave[2 * DRAW_WAVES + 1] = g;
-    s_pick[1] = -1;
-  }
-  __syncthreads();
-  const int run_w = s_pick[0];
-  if (run_w >= 0) {   // uniform
-    // pass 2: the run's blocks split over the waves
-    const int p0 = (int)((long)run_w * nblk / DRAW_WAVES), p1 = (int)((long)(run_w + 1) * nblk / DRAW_WAVES);
-    const int b0 = p0 + (int)((long)wave * (p1 - p0) / DRAW_WAVES);
-    const int b1 = p0 + (int)((long)(wave + 1) * (p1 - p0) / DRAW_WAVES);
-    const float acc = wave_sum(b1 > b0 ? lane_sum(b0, b1, lane, ld, wg) : 0.f);
-    if (lane == 0) s_wave[DRAW_WAVES + wave] = acc;
-    __syncthreads();
+  const float *trow = a.tl + ((size_t)b * (K + 1) + w.n) * V;
+  int mode = w.mode;
+  for (;;) {
     if (tid == 0) {
+      float total = 0.f, at, g;
       int pick;
-      float at, g;
-      pick_in_order(s_wave + DRAW_WAVES, DRAW_WAVES, s_wave[2 * DRAW_WAVES], s_wave[2 * DRAW_WAVES + 1],
-                    pick, at, g);
-      s_pick[2] = pick;
-      s_wave[2 * DRAW_WAVES + 2] = at;
-      s_wave[2 * DRAW_WAVES + 3] = g;
+#pragma unroll
+      for (int i = 0; i < DRAW_SLICES; ++i) total += w.sum[i];
+      pick_in_order(w.sum, DRAW_SLICES, u * total, pick, at, g);
+      s_pick = pick;
+      s_at = at;
+      s_goal = g;
+      s_found = s_last = -1;
     }
     __syncthreads();
-    // pass 3: the share that holds the goal, walked by its wave
-    if (wave == s_pick[2]) {
-      float run = s_wave[2 * DRAW_WAVES + 2];
-      const float goal = s_wave[2 * DRAW_WAVES + 3];
-      int found = -1, last = -1;
-      for (int blk = b0; blk < b1 && found < 0; ++blk) {
-        float v[4];
-        wg(ld(blk * 256 + 4 * lane), blk * 256 + 4 * lane, v);
-        const float ls = (v[0] + v[1]) + (v[2] + v[3]);
-        float x = ls;   // inclusive prefix over the lanes, fixed order
+    if (s_pick >= 0 || mode == 0) break;    // uniform
+    mode = 0;
+    for (int p = 0; p < DRAW_SLICES; ++p) {
+      int lo, hi;
+      slice_of(V, p, DRAW_SLICES, lo, hi);
+      const float sum = block_sum(slice_weight(a, w, 0, trow, trow, lo, hi), sh);
+      if (tid == 0) w.sum[p] = sum;
+    }
+    __syncthreads();
+  }
+  if (s_pick >= 0) {   // uniform
+    const float *drow = mode == 1 ? a.dl + ((size_t)b * K + w.n) * V : trow;
+    int lo, hi;
+    slice_of(V, s_pick, DRAW_SLICES, lo, hi);
+    float run = s_at;
+    const float goal = s_goal;
+    for (int c = lo; c < hi && s_found < 0; c += 4096) {   // s_found: uniform past the barrier
+      const int i0 = c + 16 * tid;
+      f32x4 t[4], d[4], v[4];
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const float t = __shfl_up(x, o, 64);
-          if (lane >= o) x += t;
-        }
-        const unsigned long long hit = __ballot(ls > 0.f && run + x > goal);
-        const unsigned long long nz = __ballot(ls > 0.f);
-        if (nz) {
-          const int l = 63 - __clzll((long long)nz);
-          const float vl[4] = {__shfl(v[0], l, 64), __shfl(v[1], l, 64), __shfl(v[2], l, 64),
-                               __shfl(v[3], l, 64)};
-          for (int q = 3; q >= 0; --q)
-            if (vl[q] > 0.f) { last = blk * 256 + 4 * l + q; break; }
-        }
-        if (hit) {
-          const int l = __ffsll((long long)hit) - 1;
-          float r = run + __shfl(x, l, 64) - __shfl(ls, l, 64);   // prefix before lane l
-          const float vl[4] = {__shfl(v[0], l, 64), __shfl(v[1], l, 64), __shfl(v[2], l, 64),
-                               __shfl(v[3], l, 64)};
-          int id = -1, lastl = -1;
-          for (int q = 0; q < 4; ++q) {
-            if (vl[q] > 0.f) lastl = blk * 256 + 4 * l + q;
-            if (vl[q] > 0.f && r + vl[q] > goal) { id = blk * 256 + 4 * l + q; break; }
-            r += vl[q];
-          }
-          found = id >= 0 ? id : lastl;
-        }
-        run += __shfl(x, 63, 64);
+      for (int q = 0; q < 4; ++q) {
+        const int i = i0 + 4 * q < hi ? i0 + 4 * q : lo;
+        t[q] = *(const f32x4 *)(trow + i);
+        d[q] = mode == 1 ? *(const f32x4 *)(drow + i) : t[q];
       }
-      if (lane == 0) s_pick[1] = found >= 0 ? found : last;
+      float ls = 0.f;
+      int last = -1;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        v[q] = i0 + 4 * q < hi ? draw_weights(w, mode, t[q], d[q], a.inv_t) : f32x4{0.f, 0.f, 0.f, 0.f};
+        ls += (v[q].x + v[q].y) + (v[q].z + v[q].w);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (v[q][e] > 0.f) last = i0 + 4 * q + e;
+      }
+      float x = ls;   // inclusive prefix over the lanes, then over the waves, in order
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const float y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+      }
+      if (lane == 63) s_wave[wave] = x;
+      __syncthreads();
+      float base = run;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (q < wave) base += s_wave[q];
+        run += s_wave[q];
+      }
+      if (last >= 0) atomicMax(&s_last, last);
+      // the lowest thread past the goal (ids ascend with the thread)
+      const unsigned long long hit = __ballot(ls > 0.f && base + x > goal);
+      if (hit && lane == __ffsll((long long)hit) - 1) {
+        float at = base + x - ls;
+        int id = -1;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (id < 0 && v[q][e] > 0.f && at + v[q][e] > goal) id = i0 + 4 * q + e;
+            at += v[q][e];
+          }
+        atomicMin((unsigned *)&s_found, (unsigned)(id >= 0 ? id : last));   // -1: the largest unsigned
+      }
+      __syncthreads();
     }
   }
-  __syncthreads();
-  return s_pick[1];
+  if (tid == 0) {
+    a.n_acc[b] = w.n;
+    a.next[b] = s_pick < 0 ? -1 : s_found >= 0 ? s_found : s_last;
+  }
 }
 
-struct VerifyChainArgs {
-  int K, V;
-  float inv_t;                   // 0: greedy
-  const float *tl, *dl;          // [B, K+1, V], [B, K, V]
-  const RowStat *ts, *ds;        // [B*(K+1)][VSPLIT], [B*K][VSPLIT]
-  const int32_t *drafts;         // [B, K]
-  const float *u;                // [B, K+1]
-  int32_t *n_acc, *next;         // [B]
-  uint32_t *err;
-};
-
-constexpr int VER_MAXK = 64;     // drafts per sequence (max_steps <= 63)
-
-__global__ __launch_bounds__(DRAW_THREADS) void k_verify_chain(VerifyChainArgs a) {
-  __shared__ float s_wave[DRAW_SHARED];
-  __shared__ int s_pick[3];
-  __shared__ RowSum s_t[VER_MAXK + 1], s_d[VER_MAXK];
-  __shared__ int s_x[VER_MAXK];
-  __shared__ float s_lt[VER_MAXK], s_ld[VER_MAXK];
-  __shared__ int s_n, s_mode;
-  const int b = blockIdx.x, tid = threadIdx.x;
-  const int K = a.K, V = a.V;
-  const bool sampled = a.inv_t > 0.f;
-  // row statistics and the drafts' own logits, in parallel
-  if (tid <= K) s_t[tid] = merge_row(a.ts + ((size_t)b * (K + 1) + tid) * VSPLIT);
-  if (sampled && tid < K) s_d[tid] = merge_row(a.ds + ((size_t)b * K + tid) * VSPLIT);
-  if (tid < K) {
-    const int x = a.drafts[(size_t)b * K + tid];
-    const bool ok = x >= 0 && x < V;
-    s_x[tid] = ok ? x : -1;
-    if (!ok) atomicOr(a.err, ERRF_TOKEN);
-    if (sampled) {
-      s_lt[tid] = ok ? a.tl[((size_t)b * (K + 1) + tid) * V + x] : 0.f;
-      s_ld[tid] = ok ? a.dl[((size_t)b * K + tid) * V + x] : 0.f;
+// Greedy: one wave per sequence, lane i takes row i's arg-max; the first
+// draft that is not its row's choice is one ballot.
+__global__ __launch_bounds__(64) void k_verify_greedy(VerifyChainArgs a) {
+  const int b = blockIdx.x, lane = threadIdx.x, K = a.K;   // K <= 63
+  const int arg = lane <= K ? merge_best(a.best + ((size_t)b * (K + 1) + lane) * a.parts, a.parts) : -1;
+  int x = -1;
+  if (lane < K) {
+    x = a.drafts[(size_t)b * K + lane];
+    if (x < 0 || x >= a.V) {
+      atomicOr(a.err, ERRF_TOKEN);
+      x = -1;
     }
   }
-  __syncthreads();
-  if (tid == 0) {
-    int n = 0, mode = 0;         // mode 0: draw from p_target row n; 1: the residual at n
-    for (; n < K; ++n) {
-      const int x = s_x[n];
-      if (x < 0) break;          // an invalid draft is never kept
-      if (!sampled) {
-        if (s_t[n].arg != x) break;
-      } else {
-        const float pt = expf(s_lt[n] * a.inv_t - s_t[n].M) / s_t[n].S;
-        const float pd = expf(s_ld[n] * a.inv_t - s_d[n].M) / s_d[n].S;
-        const float r = a.u[(size_t)b * (K + 1) + n];
-        if (!(r < fminf(1.f, pt / pd))) { mode = 1; break; }
-      }
-    }
-    s_n = n;
-    s_mode = mode;
-  }
-  __syncthreads();
-  const int n = s_n;
-  int next;
-  if (!sampled) {
-    next = s_t[n].arg;
-  } else {
-    const float it = a.inv_t, u = a.u[(size_t)b * (K + 1) + K];
-    const RowSum t = s_t[n];
-    const float *trow = a.tl + ((size_t)b * (K + 1) + n) * V;
-    // V is a multiple of 16, so ids i0..i0+3 are all inside or all past the
-    // row; the loads are unconditional (clamped to id 0, masked), so that a
-    // batch of blocks keeps its loads in flight together
-    auto lt = [&](int i0) {   // the target row's values (clamped past the row)
-      DrawRaw r;
-      r.x = *(const f32x4 *)(trow + (i0 < V ? i0 : 0));
-      r.y = r.x;
-      return r;
-    };
-    auto wt = [&](const DrawRaw &r, int i0, float (&v)[4]) {   // p_target up to its normaliser
-      const bool in = i0 < V;
-      v[0] = in ? expf(r.x.x * it - t.M) : 0.f; v[1] = in ? expf(r.x.y * it - t.M) : 0.f;
-      v[2] = in ? expf(r.x.z * it - t.M) : 0.f; v[3] = in ? expf(r.x.w * it - t.M) : 0.f;
-    };
-    if (s_mode == 1) {   // max(0, p_target - p_draft) at the rejected position
-      const RowSum d = s_d[n];
-      const float *drow = a.dl + ((size_t)b * K + n) * V;
-      const float ist = 1.f / t.S, isd = 1.f / d.S;
-      auto lr = [&](int i0) {   // both rows' values (clamped past the row)
-        DrawRaw r;
-        r.x = *(const f32x4 *)(trow + (i0 < V ? i0 : 0));
-        r.y = *(const f32x4 *)(drow + (i0 < V ? i0 : 0));
-        return r;
-      };
-      auto wr = [&](const DrawRaw &r, int i0, float (&v)[4]) {
-        const bool in = i0 < V;
-        const float p[4] = {r.x.x, r.x.y, r.x.z, r.x.w}, q4[4] = {r.y.x, r.y.y, r.y.z, r.y.w};
-        for (int q = 0; q < 4; ++q)
-          v[q] = in ? fmaxf(0.f, expf(p[q] * it - t.M) * ist - expf(q4[q] * it - d.M) * isd) : 0.f;
-      };
-      next = draw_ids(V, u, lr, wr, s_wave, s_pick);
-      if (next < 0) next = draw_ids(V, u, lt, wt, s_wave, s_pick);   // identical distributions
-    } else {
-      next = draw_ids(V, u, lt, wt, s_wave, s_pick);
-    }
-  }
-  if (tid == 0) {
+  const int n = __ffsll((long long)__ballot(lane >= K || x < 0 || x != arg)) - 1;
+  const int next = __shfl(arg, n, 64);
+  if (lane == 0) {
     a.n_acc[b] = n;
     a.next[b] = next;
   }
 }
 
 struct VerifyTreeArgs {
-  int nodes, V;
-  const RowStat *ts;             // [B*(nodes+1)][VSPLIT]
+  int nodes, V, parts;
+  const BestStat *ts;            // [B*(nodes+1)][parts]
   const int32_t *tokens, *parent;   // [B, nodes]
   int32_t *n_acc, *path, *next;  // [B], [B, nodes], [B]
 };
@@ -369,7 +445,7 @@ struct VerifyTreeArgs {
 __global__ __launch_bounds__(64) void k_verify_tree(VerifyTreeArgs a) {
   __shared__ int s_arg[MAX_VERIFY_NODES + 1];
   const int b = blockIdx.x, lane = threadIdx.x, v = a.nodes;
-  for (int j = lane; j <= v; j += 64) s_arg[j] = merge_row(a.ts + ((size_t)b * (v + 1) + j) * VSPLIT).arg;
+  for (int j = lane; j <= v; j += 64) s_arg[j] = merge_best(a.ts + ((size_t)b * (v + 1) + j) * a.parts, a.parts);
   const int tok = lane < v ? a.tokens[(size_t)b * v + lane] : -1;
   const int par = lane < v ? a.parent[(size_t)b * v + lane] : -2;
   __syncthreads();
@@ -390,7 +466,14 @@ __global__ __launch_bounds__(64) void k_verify_tree(VerifyTreeArgs a) {
   }
 }
 
-size_t verify_stats_bytes(int rows) { return (size_t)rows * VSPLIT * sizeof(RowStat); }
+// Bytes of the statistics of a call over `rows` rows, and its draws: 8 per
+// (row, slice), where few rows take more slices (row_slices), and a Draw per
+// sequence of at least 3 rows (sampled, K >= 1).
+static_assert(sizeof(Draw) <= 3 * VSPLIT * sizeof(SoftStat), "draws fit beside the statistics");
+size_t verify_stats_bytes(int rows) {
+  const size_t entries = (size_t)rows * VSPLIT;
+  return 2 * sizeof(SoftStat) * (entries > VSPLIT_WGS ? entries : VSPLIT_WGS);
+}
 
 // ---------------------------------------------------------------------------
 // Chain verification that allocates nothing, for callers that cannot call
@@ -400,7 +483,7 @@ size_t verify_stats_bytes(int rows) { return (size_t)rows * VSPLIT * sizeof(RowS
 // hipGetSymbolAddress, once per device (in prism_create, or at the first
 // call on a device); host code never passes the array's own name.
 constexpr int VSTATIC_ROWS = 8192;   // logits rows statistics are kept for
-constexpr size_t VSTATIC_BYTES = 256 + (size_t)VSTATIC_ROWS * VSPLIT * sizeof(RowStat);
+constexpr size_t VSTATIC_BYTES = 256 + (size_t)VSTATIC_ROWS * VSPLIT * 2 * sizeof(SoftStat);
 static __device__ __align__(256) unsigned char scratch[VSTATIC_BYTES];
 
 namespace {
@@ -481,25 +564,36 @@ namespace prism {
 void launch_verify_chain(int B, int K, int V, float inv_t, const float *tl, const float *dl,
                          const int32_t *drafts, const float *u, int32_t *n_acc, int32_t *next,
                          void *stats, uint32_t *err, hipStream_t s) {
-  RowStat *ts = (RowStat *)stats;
-  RowStat *ds = ts + (size_t)B * (K + 1) * VSPLIT;
-  const float it = inv_t > 0.f ? inv_t : 1.f;
+  VerifyChainArgs a{};
+  a.K = K; a.V = V; a.inv_t = inv_t;
+  a.tl = tl; a.dl = dl; a.drafts = drafts; a.u = u;
+  a.n_acc = n_acc; a.next = next; a.err = err;
+  const int rt = B * (K + 1), rd = B * K;
   if (inv_t > 0.f) {   // sampled: the target and draft rows' softmax statistics
-    hipLaunchKernelGGL(k_rows_stats<true>, dim3(VSPLIT, B * (K + 1)), dim3(256), 0, s, tl, V, it, ts);
-    hipLaunchKernelGGL(k_rows_stats<true>, dim3(VSPLIT, B * K), dim3(256), 0, s, dl, V, it, ds);
+    a.parts = row_slices(rt + rd);
+    SoftStat *st = (SoftStat *)stats;
+    a.ts = st;
+    a.ds = st + (size_t)rt * a.parts;
+    const size_t entries = (size_t)(rt + rd) * a.parts;
+    a.draw = (Draw *)(st + entries);
+    hipLaunchKernelGGL(k_rows_soft, dim3(a.parts, rt + rd), dim3(256), 0, s, tl, rt, dl, V, inv_t, st);
+    hipLaunchKernelGGL(k_verify_decide, dim3(DRAW_SLICES, B), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_verify_draw, dim3(B), dim3(256), 0, s, a);
   } else {             // greedy: the target rows' arg-max only
-    hipLaunchKernelGGL(k_rows_stats<false>, dim3(VSPLIT, B * (K + 1)), dim3(256), 0, s, tl, V, it, ts);
+    a.parts = row_slices(rt);
+    a.best = (const BestStat *)stats;
+    hipLaunchKernelGGL(k_rows_best, dim3(a.parts, rt), dim3(256), 0, s, tl, V, (BestStat *)stats);
+    hipLaunchKernelGGL(k_verify_greedy, dim3(B), dim3(64), 0, s, a);
   }
-  VerifyChainArgs a{K, V, inv_t, tl, dl, ts, ds, drafts, u, n_acc, next, err};
-  hipLaunchKernelGGL(k_verify_chain, dim3(B), dim3(DRAW_THREADS), 0, s, a);
 }
 
 void launch_verify_tree(int B, int nodes, int V, const float *tl, const int32_t *tokens,
                         const int32_t *parent, int32_t *n_acc, int32_t *path, int32_t *next,
                         void *stats, hipStream_t s) {
-  RowStat *ts = (RowStat *)stats;
-  hipLaunchKernelGGL(k_rows_stats<false>, dim3(VSPLIT, B * (nodes + 1)), dim3(256), 0, s, tl, V, 1.f, ts);
-  VerifyTreeArgs a{nodes, V, ts, tokens, parent, n_acc, path, next};
+  const int rows = B * (nodes + 1), parts = row_slices(rows);
+  BestStat *ts = (BestStat *)stats;
+  hipLaunchKernelGGL(k_rows_best, dim3(parts, rows), dim3(256), 0, s, tl, V, ts);
+  VerifyTreeArgs a{nodes, V, parts, ts, tokens, parent, n_acc, path, next};
   hipLaunchKernelGGL(k_verify_tree, dim3(B), dim3(64), 0, s, a);
 }
 
