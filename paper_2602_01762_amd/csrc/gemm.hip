@@ -26,26 +26,50 @@
 
 namespace prism {
 
+// B fragments of the operand rows: bf16 planes come tiled, one contiguous KiB
+// per (row tile, k-block, plane) (read from row-major planes, each load
+// touched 16 half lines: with the shared epilogue of the unsplit products,
+// 32-row gate/up 55.1 -> 51.0 us at 8B and 161.7 -> 151.0 at 70B, 70B LM head
+// 328.6 -> 319.2);
+// fp32 rows are row-major, rows past R read as zero.
+template <typename T, int RT, bool PAIR>
+struct BSrc {
+  const T *h[RT], *l[RT];
+  bool ok[RT];
+  __device__ __forceinline__ BSrc(const Act &x, int R) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      size_t off;
+      if constexpr (sizeof(T) == 2) {
+        ok[rt] = true;
+        off = ((size_t)rt * (x.ld / 32) * 64 + lane) * 8;
+      } else {
+        const int r = (lane & 15) + 16 * rt;
+        ok[rt] = r < R;
+        off = (size_t)(ok[rt] ? r : 0) * x.ld + (lane >> 4) * Ty<T>::E;
+      }
+      h[rt] = (const T *)x.hi + off;
+      l[rt] = PAIR ? (const T *)x.lo + off : nullptr;
+    }
+  }
+  __device__ __forceinline__ u32x4 get(const T *p, bool live, int kb) const {
+    constexpr int step = sizeof(T) == 2 ? 512 : Ty<T>::KB;
+    if constexpr (sizeof(T) == 2) return *(const u32x4 *)(p + (size_t)kb * step);
+    else return live ? *(const u32x4 *)(p + (size_t)kb * step) : u32x4{0, 0, 0, 0};
+  }
+  __device__ __forceinline__ u32x4 hi(int rt, int kb) const { return get(h[rt], ok[rt], kb); }
+  __device__ __forceinline__ u32x4 lo(int rt, int kb) const { return get(l[rt], ok[rt], kb); }
+};
+
 template <typename T, int RT, int NT, bool PAIR>
 __device__ __forceinline__ void mainloop(const u32x4 *__restrict__ w0, int nkb, const Act &x,
                                          int R, int kb0, int kb1, f32x4 (&acc)[NT][RT]) {
-  constexpr int E = Ty<T>::E, KB = Ty<T>::KB;
   // k-blocks in flight: about 96 VGPRs of A and B fragments per lane
   constexpr int U0 = 24 / (NT + (PAIR ? 2 : 1) * RT);
   constexpr int U = U0 > 8 ? 8 : (U0 < 1 ? 1 : U0);
   const int lane = threadIdx.x & 63;
-  const int col = lane & 15, kq = lane >> 4;
-  const T *xh[RT];
-  const T *xl[RT];
-  bool ok[RT];
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    const int r = col + 16 * rt;
-    ok[rt] = r < R;
-    const size_t off = (size_t)(ok[rt] ? r : 0) * x.ld + kq * E;
-    xh[rt] = (const T *)x.hi + off;
-    xl[rt] = PAIR ? (const T *)x.lo + off : nullptr;
-  }
+  const BSrc<T, RT, PAIR> bx(x, R);
   const u32x4 *wp[NT];
 #pragma unroll
   for (int n = 0; n < NT; ++n) wp[n] = w0 + ((size_t)n * nkb + kb0) * 64 + lane;
@@ -64,10 +88,8 @@ __device__ __forceinline__ void mainloop(const u32x4 *__restrict__ w0, int nkb, 
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        const size_t o = (size_t)(kb + u) * KB;
-        const bool ld = ok[rt] && u < nb;
-        bh[u][rt] = ld ? *(const u32x4 *)(xh[rt] + o) : z4;
-        if (PAIR) bl[u][rt] = ld ? *(const u32x4 *)(xl[rt] + o) : z4;
+        bh[u][rt] = u < nb ? bx.hi(rt, kb + u) : z4;
+        if (PAIR) bl[u][rt] = u < nb ? bx.lo(rt, kb + u) : z4;
       }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -92,26 +114,13 @@ __device__ __forceinline__ void mainloop(const u32x4 *__restrict__ w0, int nkb, 
 template <typename T, int RT, int NT, bool PAIR>
 __device__ __forceinline__ void mainloop_db(const u32x4 *__restrict__ w0, int nkb, const Act &x,
                                             int R, int kb0, int kb1, f32x4 (&acc)[NT][RT]) {
-  constexpr int E = Ty<T>::E, KB = Ty<T>::KB;
   constexpr int U0 = 24 / (NT + (PAIR ? 2 : 1) * RT);
   constexpr int U = U0 > 8 ? 8 : (U0 < 1 ? 1 : U0);
   const int lane = threadIdx.x & 63;
-  const int col = lane & 15, kq = lane >> 4;
-  const T *xh[RT];
-  const T *xl[RT];
-  bool ok[RT];
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    const int r = col + 16 * rt;
-    ok[rt] = r < R;
-    const size_t off = (size_t)(ok[rt] ? r : 0) * x.ld + kq * E;
-    xh[rt] = (const T *)x.hi + off;
-    xl[rt] = PAIR ? (const T *)x.lo + off : nullptr;
-  }
+  const BSrc<T, RT, PAIR> bx(x, R);
   const u32x4 *wp[NT];
 #pragma unroll
   for (int n = 0; n < NT; ++n) wp[n] = w0 + (size_t)n * nkb * 64 + lane;
-  const u32x4 z4 = {0, 0, 0, 0};
   u32x4 a[2][U][NT], bh[2][U][RT], bl[2][U][RT];
   auto load = [&](int s, int kb) {
 #pragma unroll
@@ -121,9 +130,8 @@ __device__ __forceinline__ void mainloop_db(const u32x4 *__restrict__ w0, int nk
       for (int n = 0; n < NT; ++n) a[s][u][n] = __builtin_nontemporal_load(wp[n] + (size_t)k * 64);
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        const size_t o = (size_t)k * KB;
-        bh[s][u][rt] = ok[rt] ? *(const u32x4 *)(xh[rt] + o) : z4;
-        if (PAIR) bl[s][u][rt] = ok[rt] ? *(const u32x4 *)(xl[rt] + o) : z4;
+        bh[s][u][rt] = bx.hi(rt, k);
+        if (PAIR) bl[s][u][rt] = bx.lo(rt, k);
       }
     }
   };
@@ -681,7 +689,8 @@ template <typename T, int RT, int NT, bool PAIR, int EPI_K, int VR>
 __global__ __launch_bounds__((gemm_max_threads<RT, NT>())) void k_gemm(GemmLaunch g) {
   constexpr bool GX = EPI_K == EPI_NORM_GATHER;
   constexpr int EPI = GX ? EPI_NORM : EPI_K;
-  // dynamic LDS: [(kw - 1) * NT * RT * 64] f32x4 partial sums, kw floats,
+  // dynamic LDS: [(kw - 1) * NT * RT * 64] f32x4 partial sums (kw with
+  // several tiles), kw floats,
   // then (GEMV path, VR > 0) VR * K floats of staged activations
   extern __shared__ f32x4 red[];
   __shared__ float rowscale[MAX_ROWS];
@@ -734,13 +743,18 @@ __global__ __launch_bounds__((gemm_max_threads<RT, NT>())) void k_gemm(GemmLaunc
       mainloop<T, RT, NT, PAIR>((const u32x4 *)m.w + (size_t)t0 * m.nkb * 64, m.nkb, g.x, g.R, kb0,
                                 kb1, acc);
   }
-  if (kw > 1) {
-    if (wave > 0) {
+  // Several accumulator tiles (batched unsplit products): every wave leaves
+  // its sums in LDS and takes every kw-th tile through the reduction and the
+  // epilogue (wave 0 alone did both, after the weight stream had ended).  The
+  // sums are added in wave order either way.
+  constexpr int NP = NT * RT;
+  const bool share = NP > 1 && kw > 1;
+  if (kw > 1 && (share || wave > 0)) {
 #pragma unroll
-      for (int n = 0; n < NT; ++n)
+    for (int n = 0; n < NT; ++n)
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) red[(((wave - 1) * NT + n) * RT + rt) * 64 + lane] = acc[n][rt];
-    }
+      for (int rt = 0; rt < RT; ++rt)
+        red[((share ? wave : wave - 1) * NP + n * RT + rt) * 64 + lane] = acc[n][rt];
   }
   if (own_scales) {
     __syncthreads();
@@ -748,27 +762,37 @@ __global__ __launch_bounds__((gemm_max_threads<RT, NT>())) void k_gemm(GemmLaunc
   } else if (kw > 1) {
     __syncthreads();
   }
+  auto finish = [&](int n, int rt, f32x4 a, long cb, int rp) {
+    const int r = (lane & 15) + 16 * rt;
+    const float sc = has_norm && r < g.R ? (own_scales ? rowscale[r] : g.norm.scale[r]) : 1.f;
+    f32x4 tadd = GX ? tv : f32x4{0.f, 0.f, 0.f, 0.f};
+    if (EPI == EPI_NORM && !GX && g.tab && r < g.R) {   // batched rows: tokens from the prep
+      const int t = g.tab_tok[r];
+      if (t >= 0) tadd = *(const f32x4 *)(g.tab + (size_t)t * m.N + (t0 + n) * 16 + 4 * (lane >> 4));
+    }
+    const float ss = epilogue_tile<T, EPI>(g, t0 + n, r, a, sc, cb, rp, tadd);
+    if (EPI == EPI_NORM && r < g.R && lane < 16) g.ss[(size_t)(t0 + n) * g.R + r] = ss;
+  };
+  if constexpr (NP > 1) {
+    if (share) {
+      for (int p = wave; p < NP; p += kw) {
+        f32x4 a = red[p * 64 + lane];
+        for (int j = 1; j < kw; ++j) a += red[(j * NP + p) * 64 + lane];
+        finish(p / RT, p % RT, a, cbase[0], rpos[0]);   // (QKV: one tile, below)
+      }
+      return;
+    }
+  }
   if (wave != 0) return;
   for (int j = 1; j < kw; ++j)
 #pragma unroll
     for (int n = 0; n < NT; ++n)
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) acc[n][rt] += red[(((j - 1) * NT + n) * RT + rt) * 64 + lane];
-
 #pragma unroll
   for (int n = 0; n < NT; ++n)
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const int r = (lane & 15) + 16 * rt;
-      const float sc = has_norm && r < g.R ? (own_scales ? rowscale[r] : g.norm.scale[r]) : 1.f;
-      f32x4 tadd = GX ? tv : f32x4{0.f, 0.f, 0.f, 0.f};
-      if (EPI == EPI_NORM && !GX && g.tab && r < g.R) {   // batched rows: tokens from the prep
-        const int t = g.tab_tok[r];
-        if (t >= 0) tadd = *(const f32x4 *)(g.tab + (size_t)t * m.N + (t0 + n) * 16 + 4 * (lane >> 4));
-      }
-      const float ss = epilogue_tile<T, EPI>(g, t0 + n, r, acc[n][rt], sc, cbase[rt], rpos[rt], tadd);
-      if (EPI == EPI_NORM && r < g.R && lane < 16) g.ss[(size_t)(t0 + n) * g.R + r] = ss;
-    }
+    for (int rt = 0; rt < RT; ++rt) finish(n, rt, acc[n][rt], cbase[rt], rpos[rt]);
 }
 
 // Token of row i for a K-split fusion FC that has no prep pass: wave 0 of
@@ -870,20 +894,16 @@ __global__ __launch_bounds__(256) void k_gemm_split_lds(GemmLaunch g) {
   const int kb0 = g.kb_lo + (int)((long)sl * nk / S), kb1 = g.kb_lo + (int)((long)(sl + 1) * nk / S);
   const int nf = (kb1 - kb0) * 2 * RT;    // <= SPLIT_LDS_FRAGS (checked by the launcher)
   const SplitTok stok = split_tok_issue(g);   // wave 0 is live in every workgroup
-  // staging loads: fragment f = (k-block i, plane p, row tile rt), lane (row
-  // 16 rt + (lane & 15), k 8 (lane >> 4)); unconditional (clamped) so that
-  // the weight loads issued after them stay in flight
+  // staging loads: fragment f = (k-block i, plane p, row tile rt) as it is
+  // tiled; unconditional (clamped) so that the weight loads issued after them
+  // stay in flight
   u32x4 sv[SF];
 #pragma unroll
   for (int i = 0; i < SF; ++i) {
     const int f = max(min(wave + 4 * i, nf - 1), 0);
     const int kbi = f / (2 * RT), pl = (f / RT) & 1, rt = f % RT;
-    const int r = (lane & 15) + 16 * rt;
     const int kb = min(kb0 + kbi, m.nkb - 1);
-    const bf16_t *src = (const bf16_t *)(pl ? g.x.lo : g.x.hi) + (size_t)(r < g.R ? r : 0) * g.x.ld +
-                        (size_t)kb * 32 + 8 * (lane >> 4);
-    sv[i] = *(const u32x4 *)src;
-    if (r >= g.R) sv[i] = u32x4{0, 0, 0, 0};
+    sv[i] = ((const u32x4 *)(pl ? g.x.lo : g.x.hi))[((size_t)rt * (g.x.ld / 32) + kb) * 64 + lane];
   }
   const u32x4 *wp[NT];
 #pragma unroll
@@ -1194,7 +1214,9 @@ template <typename T, int RT, int NT, bool PAIR, int VR>
 static bool gemm_epi(const GemmLaunch &g, hipStream_t s) {
   if (g.kw < 1 || 64 * g.kw > gemm_max_threads<RT, NT>()) return false;
   dim3 grid(g.m.n_tiles / NT);
-  size_t lds = (size_t)((g.kw - 1) * NT * RT * 64) * sizeof(f32x4) +
+  if (NT * RT > 1 && g.kw > 1 && g.epi == EPI_QKV) return false;   // its rows' slots are wave 0's
+  const int parts = NT * RT > 1 && g.kw > 1 ? g.kw : g.kw - 1;     // partial sums kept per tile
+  size_t lds = (size_t)(parts * NT * RT * 64) * sizeof(f32x4) +
                (size_t)64 * g.kw * sizeof(float);
   if (VR > 0) lds += (size_t)VR * g.m.K * sizeof(float);
   if constexpr (VR > 0) {

@@ -46,12 +46,12 @@ struct TiledMat {
 // hi = bf16(x), lo = bf16(x - hi) (two planes), both fed to the MFMA, so the
 // product sees x to within 2^-17 relative.
 //
-// Passes of more than MAX_ROWS rows (bf16) keep the planes tiled (pk): the
-// 16 rows x 32 columns of one MFMA B fragment are one contiguous KiB in
-// operand order, [rows / 16][ld / 32][64 lanes][8 values], so that the tile
-// kernel moves a fragment to LDS with one coalesced load per wave.  The rows
-// of the last tile past R are allocated and hold anything: column j of a
-// product reaches output row j only, which is not stored.
+// The matrix-core products of bf16 models take the planes tiled (pk): the 16
+// rows x 32 columns of one MFMA B fragment are one contiguous KiB in operand
+// order, [rows / 16][ld / 32][64 lanes][8 values], one coalesced load per
+// wave.  The rows of the last tile past R are allocated and hold anything:
+// column j of a product reaches output row j only, which is not stored.  The
+// GEMV and fp32 models read row-major planes.
 struct Act {
   const void *hi = nullptr;
   const void *lo = nullptr;
@@ -63,8 +63,10 @@ struct ActOut {
   void *lo = nullptr;
   int ld = 0;
   int pk = 0;
-  // element (r, c); 8 columns from a multiple of 8 are contiguous either way
+  int c0 = 0;   // column of the operand that c = 0 names
+  // element (r, c0 + c); 8 columns from a multiple of 8 are contiguous either way
   __host__ __device__ size_t at(int r, int c) const {
+    c += c0;
     if (!pk) return (size_t)r * ld + c;
     return ((size_t)(r >> 4) * (ld >> 5) + (c >> 5)) * 512 + ((c >> 3) & 3) * 128 + (r & 15) * 8 + (c & 7);
   }

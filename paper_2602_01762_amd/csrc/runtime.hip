@@ -571,10 +571,11 @@ static Act act_of(const ActOut &o, int ld) {
   return a;
 }
 
-// operand planes of a pass over R rows: tiled for the tile kernel
-static ActOut planes_for(const prism_ctx *c, ActOut o, int ld, int R) {
+// operand planes with rows of ld columns: tiled for the matrix-core kernels
+// of bf16 models, row-major for the GEMV (and fp32)
+static ActOut planes_for(const prism_ctx *c, ActOut o, int ld, bool gemv) {
   o.ld = ld;
-  o.pk = c->bf16 && R > MAX_ROWS;
+  o.pk = c->bf16 && !gemv;
   return o;
 }
 
@@ -618,6 +619,16 @@ static GemmLaunch gemm_of(const prism_ctx *c, const TiledMat &m, const Act &x, i
   return g;
 }
 
+// whether a product runs on the GEMV
+static bool is_gemv(const prism_ctx *c, const TiledMat &m, int R, int epi, int kb_lo = 0) {
+  return gemm_of(c, m, Act{}, R, epi, kb_lo).gemv != 0;
+}
+// whether the LM head does: whole batches of 16 k-blocks (H a multiple of 512)
+static bool lm_is_gemv(const prism_ctx *c, int R) {
+  return c->bf16 && R <= LM_GEMV_MAX_ROWS && c->lm.nkb % 16 == 0 &&
+         gemv_lds_bytes(R, c->H) + 64 * 1024 <= c->lds_limit;
+}
+
 // measurement: an event pair around the next launches of class `what`
 // (-1: not profiled, or no event pair left)
 static int prof_begin(prism_ctx *c, int what, hipStream_t s) {
@@ -641,11 +652,10 @@ static void gemm_go(prism_ctx *c, const GemmLaunch &g, hipStream_t s) {
 // the feature columns are multiplied for the R / fc_div trees only, and the
 // finish pass writes every row (its tree's product plus its token's table
 // row).  8B, 4 trees of 61 rows: 52 -> 28 us against 244 rows multiplied.
-static int enqueue_fc_trees(prism_ctx *c, const Pass &p, hipStream_t s) {
+static int enqueue_fc_trees(prism_ctx *c, const Pass &p, const ActOut &ug, hipStream_t s) {
   const Set &S = c->sets[p.set];
   const int H = c->H, nt = p.R / p.fc_div, kb_lo = H / 32;
-  ActOut X = c->xfc;
-  X.ld = H + p.F;
+  const ActOut X = planes_for(c, c->xfc, H + p.F, false);
   RowsIn in = p.in;
   in.feat_rows = nullptr;
   launch_fc_prep(true, nt, in, TokFromLm{}, c->embed, c->V, H, p.F, X, c->err, nullptr, true, s);
@@ -663,7 +673,7 @@ static int enqueue_fc_trees(prism_ctx *c, const Pass &p, hipStream_t s) {
   g.part_rows = nt;
   g.epi = EPI_NORM;
   g.tab = S.tab; g.tab_tok = p.in.tokens; g.tab_V = c->V; g.err = c->err;
-  g.y = c->u; g.ldy = H; g.gain = S.g1; g.g = planes_for(c, c->ug, H, p.R); g.ss = c->ss_u;
+  g.y = c->u; g.ldy = H; g.gain = S.g1; g.g = ug; g.ss = c->ss_u;
   launch_gemm_finish(g, s);
   prof_end(c, pr, s);
   return gemm_ss_parts(g);
@@ -675,17 +685,17 @@ static void enqueue_front(prism_ctx *c, const Pass &p, const KvArgs &kv, hipStre
   const Set &S = c->sets[p.set];
   const bool bf = c->bf16;
   const int R = p.R, H = c->H;
-  const ActOut ug = planes_for(c, c->ug, H, R);
+  const ActOut ug = planes_for(c, c->ug, H, is_gemv(c, S.qkv, R, EPI_QKV));
   int parts_u;
   GemmLaunch g;
   if (p.fc_div) {
-    parts_u = enqueue_fc_trees(c, p, s);
+    parts_u = enqueue_fc_trees(c, p, ug, s);
   } else {
     // fusion FC: u = W_fc [E(x) ; f]  ->  u, (u * g1), sums of squares
-    const ActOut X = planes_for(c, c->xfc, H + p.F, R);
     // with the set's embedding table the product covers the feature columns
     // only, and its epilogue adds the table row of each row's token
     const int kb_lo = S.tab_ready ? H / (bf ? 32 : 16) : 0;
+    const ActOut X = planes_for(c, c->xfc, H + p.F, is_gemv(c, S.fc, R, EPI_NORM, kb_lo));
     g = gemm_of(c, S.fc, act_of(X, H + p.F), R, EPI_NORM, kb_lo);
     if (S.tab_ready) g.tab = S.tab;
     if (g.gemv) {   // the GEMV stages [E(x) ; f] (or f) itself
@@ -739,6 +749,11 @@ static void enqueue_long_front(prism_ctx *c, const Pass &p, const prism_catchup 
   const Set &S = c->sets[p.set];
   const int H = c->H, F = p.F, T = cu.total_rows;
   const int chunks = (T + c->long_max - 1) / c->long_max;
+  int tile0;
+  const TiledMat kvm = qkv_part(c, S.qkv, false, tile0);
+  const int kv_tile0 = tile0;
+  const TiledMat qm = qkv_part(c, S.qkv, true, tile0);
+  const ActOut qx = planes_for(c, c->r1g, H, is_gemv(c, qm, B, EPI_QKV));
   for (int i = 0; i < chunks; ++i) {
     const int r0 = (int)((long)i * T / chunks), n = (int)((long)(i + 1) * T / chunks) - r0;
     RowsIn in{};
@@ -750,26 +765,22 @@ static void enqueue_long_front(prism_ctx *c, const Pass &p, const prism_catchup 
     X.ld = F;
     GemmLaunch g = gemm_of(c, S.fc, X, n, EPI_NORM, H / 32);
     g.tab = S.tab; g.tab_tok = in.tokens; g.tab_V = c->V; g.err = c->err;
-    g.y = c->u; g.ldy = H; g.gain = S.g1; g.g = planes_for(c, c->ug, H, n); g.ss = c->ss_u;
+    g.y = c->u; g.ldy = H; g.gain = S.g1; g.g = planes_for(c, c->ug, H, false); g.ss = c->ss_u;
     gemm_go(c, g, s);
     const int parts_u = gemm_ss_parts(g);
-    int tile0;
-    const TiledMat kvm = qkv_part(c, S.qkv, false, tile0);
     const ActOut ug = g.g;
     g = gemm_of(c, kvm, act_of(ug, H), n, EPI_QKV);
-    g.tile0 = tile0;
+    g.tile0 = kv_tile0;
     g.norm = norm_for(c, c->ss_u, parts_u, gemm_own_scales(g, parts_u), c->sc_u, n, s);
     g.q = c->q; g.nq = c->nq; g.nkv = c->nkv; g.d = c->d;
     g.rows = in; g.kv = kv; g.inv_freq = c->inv_freq; g.err = c->err;
     gemm_go(c, g, s);
     LastRows lr{};
     lr.idx = c->c_last; lr.r0 = r0; lr.n_src = n; lr.H = H; lr.eps = c->cfg.rms_eps;
-    lr.u = c->u; lr.gain = S.g1; lr.dst = c->u2; lr.x = planes_for(c, c->r1g, H, B); lr.scale = c->sc_r1;
+    lr.u = c->u; lr.gain = S.g1; lr.dst = c->u2; lr.x = qx; lr.scale = c->sc_r1;
     launch_last_rows(B, lr, s);
   }
-  int tile0;
-  const TiledMat qm = qkv_part(c, S.qkv, true, tile0);
-  GemmLaunch g = gemm_of(c, qm, act_of(planes_for(c, c->r1g, H, B), H), B, EPI_QKV);
+  GemmLaunch g = gemm_of(c, qm, act_of(qx, H), B, EPI_QKV);
   g.norm.scale = c->sc_r1;
   g.q = c->q2; g.nq = c->nq; g.nkv = c->nkv; g.d = c->d;
   g.rows = p.in; g.kv = kv; g.inv_freq = c->inv_freq; g.err = c->err;
@@ -784,30 +795,30 @@ static void enqueue_back(prism_ctx *c, const Pass &p, const KvArgs &kv, const fl
   const bool bf = c->bf16;
   const int R = p.R, H = c->H;
   // attention over the visible slots -> o
-  const ActOut o = planes_for(c, c->o, c->nq * c->d, R);
+  const ActOut o = planes_for(c, c->o, c->nq * c->d, is_gemv(c, S.o, R, EPI_NORM));
   launch_attention(bf, R, c->nq, c->nkv, c->d, q, p.in, kv, c->max_slots, p.grp, p.rps, c->pm, c->pl,
                    c->po, o, c->err, s);
   // r1 = u + W_o o  ->  r1, (r1 * g2), sums of squares
   GemmLaunch g = gemm_of(c, S.o, act_of(o, c->nq * c->d), R, EPI_NORM);
   g.res = u; g.ldres = H; g.y = c->r1; g.ldy = H; g.gain = S.g2;
-  g.g = planes_for(c, c->r1g, H, R);
+  g.g = planes_for(c, c->r1g, H, is_gemv(c, S.gu, R, EPI_SWIGLU));
   g.ss = c->ss_r1;
   gemm_go(c, g, s);
   const int parts_r1 = gemm_ss_parts(g);
   // z = SiLU(W_gate m) * (W_up m),  m = RMSNorm(r1; g2)
   g = gemm_of(c, S.gu, act_of(g.g, H), R, EPI_SWIGLU);
   g.norm = norm_for(c, c->ss_r1, parts_r1, gemm_own_scales(g, parts_r1), c->sc_r1, R, s);
-  g.z = planes_for(c, c->z, c->I, R);
+  g.z = planes_for(c, c->z, c->I, is_gemv(c, S.down, R, EPI_NORM));
   gemm_go(c, g, s);
   // h = r1 + W_down z  ->  h (output), (h * g_final), sums of squares
   g = gemm_of(c, S.down, act_of(g.z, c->I), R, EPI_NORM);
   g.res = c->r1; g.ldres = H; g.y = p.hid_out; g.ldy = p.ld_hid; g.gain = c->gf;
-  g.g = p.lm_rows_x.hi ? p.lm_rows_x : c->hg;
-  g.g.ld = H; g.ss = c->ss_h;
+  const ActOut hg = p.lm_rows_x.hi ? p.lm_rows_x : planes_for(c, c->hg, H, lm_is_gemv(c, R));
+  g.g = hg;
+  g.ss = c->ss_h;
   if (p.op_out) {   // h as the next pass's FC feature columns (X[:, H:2H])
-    g.yx.hi = (bf16_t *)c->xfc.hi + H;
-    g.yx.lo = (bf16_t *)c->xfc.lo + H;
-    g.yx.ld = 2 * H;
+    g.yx = planes_for(c, c->xfc, 2 * H, false);
+    g.yx.c0 = H;
   }
   gemm_go(c, g, s);
   const int parts_h = gemm_ss_parts(g);
@@ -818,14 +829,12 @@ static void enqueue_back(prism_ctx *c, const Pass &p, const KvArgs &kv, const fl
   // logits = LM_head RMSNorm(h; g_final)  ->  top-k partials
   LmLaunch lmg{};
   lmg.m = c->lm;
-  lmg.x = act_of(c->hg, H);
+  lmg.x = act_of(hg, H);
   lmg.R = R;
   lmg.V = c->V;
   lmg.topk = p.topk;
   lmg.inv_temp = p.u ? p.inv_temp : 1.f;
-  // the GEMV LM head streams whole batches of 16 k-blocks (H a multiple of 512)
-  lmg.gemv = (c->bf16 && R <= LM_GEMV_MAX_ROWS && c->lm.nkb % 16 == 0 &&
-              gemv_lds_bytes(R, H) + 64 * 1024 <= c->lds_limit) ? 1 : 0;
+  lmg.gemv = lm_is_gemv(c, R) ? 1 : 0;
   lmg.nt = 1;
   // one row: four consecutive vocab tiles per wave when that still gives
   // about four waves per CU (longer weight streams, one round of workgroups)
@@ -1399,9 +1408,7 @@ prism_status prism_score_tree(prism_ctx *c, const prism_batch *batch, int32_t n_
       if (wide) {
         p.grp = c->score_grp;
         p.rps = rps;
-        p.lm_rows_x = c->lmr_x;
-        p.lm_rows_x.ld = c->H;
-        p.lm_rows_x.pk = 1;
+        p.lm_rows_x = planes_for(c, c->lmr_x, c->H, false);
         if (c->sets[set].tab_ready && n / rps <= MAX_ROWS) {   // one feature row per tree
           p.fc_div = rps;
           p.in.feat = (const char *)b.d_features + (size_t)(r0 / rps) * p.F * c->esz;
