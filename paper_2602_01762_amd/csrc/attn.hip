@@ -27,6 +27,7 @@ struct AttnArgs {
   const uint64_t *bits;
   KvArgs kv;
   int R, nq, nkv, d, nch, nsub;
+  int g, d_sh, span_sh;       // nq / nkv, log2 d, log2 (64 nsub)
   int grp;                    // rows per workgroup of the grouped MFMA kernel (one sequence's tree rows)
   int rps;                    // > 0: rows come in runs of rps rows of one tree each, grouped from
                               // each run's first row (its last group may be shorter)
@@ -75,10 +76,11 @@ __device__ __forceinline__ void load8(const T *p, float (&v)[8]) {
   }
 }
 
-template <typename T>
+// DK: head_dim / 32; a thread's whole K row share is loaded at once
+template <typename T, int DK>
 __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
   const int c = blockIdx.z, j = blockIdx.x, r = blockIdx.y;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = wave_id(), lane = tid & 63;
   int b, L, prefix, total;
   uint64_t bits;
   if (!row_range(a, r, b, L, prefix, total, bits)) {
@@ -87,7 +89,8 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
   }
   const int tbeg = c * ATT_S * a.nsub;
   if (tbeg >= total) return;
-  const int d = a.d, g = a.nq / a.nkv;
+  constexpr int d = 32 * DK;
+  const int g = a.g;
 
   __shared__ float qs[ATT_MAXGD];
   __shared__ float sc[ATT_MAXG][ATT_S];
@@ -102,7 +105,7 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
     l_run[tid] = 0.f;
   }
   // P.V thread layout: 8 dims per thread, dg = dim group, tg = slot group
-  const int ndg = d >> 3, G = 256 / ndg;
+  constexpr int ndg = d / 8, G = 256 / ndg;
   const int dg = tid % ndg, tg = tid / ndg;
   float acc[ATT_MAXG][8];
 #pragma unroll
@@ -118,11 +121,11 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
       const int t = t0 + tid;
       long off = -1;
       if (tid < n_here && (t < prefix || (a.bits && t >= L && ((bits >> (t - L)) & 1ull)))) {
-        const int bi = t / a.kv.bs;
+        const int bi = slot_block(a.kv, t);
         const int blk = bi < a.kv.mbps ? a.kv.block_table[(size_t)b * a.kv.mbps + bi] : -1;
         // pool layout [block, kv head, slot in block, d]
         if (blk < 0 || blk >= a.kv.n_blocks) atomicOr(a.err, ERRF_CAPACITY);
-        else off = ((long)blk * a.nkv + j) * a.kv.bs * d + (long)(t % a.kv.bs) * d;
+        else off = ((long)blk * a.nkv + j) * a.kv.bs * d + (long)slot_in_block(a.kv, t, bi) * d;
       }
       offs[tid] = off;
     }
@@ -149,25 +152,24 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
 #pragma unroll
       for (int h = 0; h < ATT_MAXG; ++h) s[h] = 0.f;
       if (off >= 0) {
-        const int dq = d >> 2;
+        constexpr int dq = d / 4;
         const T *kp = (const T *)a.kv.k_pool + off + part * dq;
-        for (int e = 0; e < dq; e += 8) {
-          float kv[8];
-          load8<T>(kp + e, kv);
+        float kv[DK][8];
+#pragma unroll
+        for (int e = 0; e < DK; ++e) load8<T>(kp + 8 * e, kv[e]);
+#pragma unroll
+        for (int e = 0; e < DK; ++e)
 #pragma unroll
           for (int h = 0; h < ATT_MAXG; ++h)
             if (h < g) {
-              const float *qh = qs + h * d + part * dq + e;
+              const float *qh = qs + h * d + part * dq + 8 * e;
 #pragma unroll
-              for (int i = 0; i < 8; ++i) s[h] += qh[i] * kv[i];
+              for (int i = 0; i < 8; ++i) s[h] += qh[i] * kv[e][i];
             }
-        }
       }
 #pragma unroll
-      for (int h = 0; h < ATT_MAXG; ++h) {
-        s[h] += __shfl_xor(s[h], 1, 64);
-        s[h] += __shfl_xor(s[h], 2, 64);
-      }
+      for (int h = 0; h < ATT_MAXG; ++h)
+        if (h < g) s[h] = group_sum(s[h], 2);
       if (part == 0) {
 #pragma unroll
         for (int h = 0; h < ATT_MAXG; ++h)
@@ -230,13 +232,14 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
     }
     __syncthreads();
   }
-  // reduce the slot groups: lanes of one wave sharing dg (butterfly over the
-  // slot-group bits of the lane index), then the waves in order
-  for (int o = ndg; o < 64; o <<= 1)
+  // reduce the slot groups: lanes of one wave sharing dg, for the heads there
+  // are (all 8 through LDS permutes cost a microsecond), then the waves in order
 #pragma unroll
-    for (int h = 0; h < ATT_MAXG; ++h)
+  for (int h = 0; h < ATT_MAXG; ++h)
+    if (h < g) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc[h][i] += __shfl_xor(acc[h][i], o, 64);
+      for (int i = 0; i < 8; ++i) acc[h][i] = stride_sum(acc[h][i], ndg);
+    }
   if (lane < ndg && tg < G) {
 #pragma unroll
     for (int h = 0; h < ATT_MAXG; ++h)
@@ -245,11 +248,11 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
         for (int i = 0; i < 8; ++i) red[wave][h * d + dg * 8 + i] = acc[h][i];
   }
   __syncthreads();
-  const int nw = (G * ndg + 63) / 64;
+  constexpr int nw = (G * ndg + 63) / 64;
   for (int e = tid; e < g * d; e += 256) {
     float sum = 0.f;
     for (int w = 0; w < nw; ++w) sum += red[w][e];
-    const int h = e / d, dim = e % d;
+    const int h = e >> a.d_sh, dim = e & (d - 1);
     a.po[(((size_t)r * a.nq + j * g + h) * a.nch + c) * d + dim] = sum;
   }
   if (tid < g) {
@@ -300,7 +303,7 @@ __global__ __launch_bounds__(256) void k_attn_mfma(AttnArgs a) {
     r = blockIdx.y / gpr * a.rps + gi * a.grp;
     gs = min(a.grp, a.rps - gi * a.grp);
   }
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = wave_id(), lane = tid & 63;
   const int col = lane & 15, q4 = lane >> 4;
   int b, L, prefix, total;
   uint64_t bits;
@@ -308,7 +311,7 @@ __global__ __launch_bounds__(256) void k_attn_mfma(AttnArgs a) {
     if (c == 0 && j == 0 && tid == 0) atomicOr(a.err, ERRF_CAPACITY);
     return;
   }
-  const int g = a.nq / a.nkv;
+  const int g = a.g;
   // column col: query head col (ungrouped), or row r + col / g, head col % g;
   // its own tree bits (grouped)
   bool cvalid = col < g;
@@ -342,8 +345,8 @@ __global__ __launch_bounds__(256) void k_attn_mfma(AttnArgs a) {
 
   // block-table entries of the chunk (at most one per slot)
   const int tend = min(total, tbeg + span);
-  const int bfirst = tbeg / bs;
-  const int nblk = (tend - 1) / bs - bfirst + 1;
+  const int bfirst = slot_block(a.kv, tbeg);
+  const int nblk = slot_block(a.kv, tend - 1) - bfirst + 1;
   for (int i = tid; i < nblk; i += 256) {
     const int bi = bfirst + i;
     s_blk[i] = bi < a.kv.mbps ? a.kv.block_table[(size_t)b * a.kv.mbps + bi] : -1;
@@ -374,13 +377,14 @@ __global__ __launch_bounds__(256) void k_attn_mfma(AttnArgs a) {
   // cache offset of slot t for this KV head, or -1 (not visible / no block)
   auto slot_off = [&](int t) -> long {
     if (t >= tend || !(t < prefix || (a.bits && t >= L && ((bits >> (t - L)) & 1ull)))) return -1;
-    const int blk = s_blk[t / bs - bfirst];
+    const int bi = slot_block(a.kv, t);
+    const int blk = s_blk[bi - bfirst];
     // pool layout [block, kv head, slot in block, d]
     if (blk < 0 || blk >= a.kv.n_blocks) {
       atomicOr(a.err, ERRF_CAPACITY);
       return -1;
     }
-    return ((long)blk * a.nkv + j) * bs * d + (long)(t % bs) * d;
+    return ((long)blk * a.nkv + j) * bs * d + (long)slot_in_block(a.kv, t, bi) * d;
   };
   // K/V rows of one slot.  The loads are unconditional (an invisible slot
   // reads slot 0 of block 0 instead, and its values are masked at use), so
@@ -550,11 +554,11 @@ __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
   row_range(a, r, b, L, prefix, total, bits);
   const int span = ATT_S * a.nsub;
   if (total > a.nch * span && h == 0 && tid == 0) atomicOr(a.err, ERRF_CAPACITY);
-  const int nch = min((total + span - 1) / span, a.nch);
+  const int nch = min((total + span - 1) >> a.span_sh, a.nch);
   const size_t base = ((size_t)r * a.nq + h) * a.nch;
   // output dims: thread = (dim, chunk group); its chunks are grp, grp + G, ...
-  const int d = a.d, G = 256 / d;
-  const int dim = tid % d, grp = tid / d;
+  const int d = a.d, G = 256 >> a.d_sh;
+  const int dim = tid & (d - 1), grp = tid >> a.d_sh;
   const bool has_grp = grp < G;
   // the first CMB_PRE partial outputs of this thread go out with the stats
   float pre[CMB_PRE];
@@ -571,7 +575,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
     wch[c] = mc;
     if (l > 0.f) m = fmaxf(m, mc);
   }
-  const float M = block_max(m, sh);        // its barriers make lch / wch visible
+  const float M = block_max<4>(m, sh);        // its barriers make lch / wch visible
   float lp = 0.f;
   for (int c = tid; c < nch; c += 256) {
     const float l = lch[c];
@@ -579,7 +583,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
     wch[c] = w;
     lp += l * w;
   }
-  const float lsum = block_sum(lp, sh);   // ends with a barrier: wch is visible
+  const float lsum = block_sum<4>(lp, sh);   // ends with a barrier: wch is visible
   float o = 0.f;
   if (has_grp) {
 #pragma unroll
@@ -615,7 +619,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
 constexpr int CMBW_MAX_CHUNKS = 8;
 template <typename T>
 __global__ __launch_bounds__(256) void k_attn_combine_w(AttnArgs a) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = wave_id(), lane = threadIdx.x & 63;
   const int h = blockIdx.x * 4 + wave, r = blockIdx.y;
   if (h >= a.nq) return;                      // whole waves; no barriers below
   int b, L, prefix, total;
@@ -623,7 +627,7 @@ __global__ __launch_bounds__(256) void k_attn_combine_w(AttnArgs a) {
   row_range(a, r, b, L, prefix, total, bits);
   const int span = ATT_S * a.nsub;
   if (total > a.nch * span && h == 0 && lane == 0) atomicOr(a.err, ERRF_CAPACITY);
-  const int nch = min((total + span - 1) / span, a.nch);   // <= CMBW_MAX_CHUNKS (launcher)
+  const int nch = min((total + span - 1) >> a.span_sh, a.nch);   // <= CMBW_MAX_CHUNKS (launcher)
   const size_t base = ((size_t)r * a.nq + h) * a.nch;
   const int d = a.d;
   // the partial outputs first, then the statistics they are weighted by
@@ -693,6 +697,9 @@ void launch_attention(bool bf16, int R, int nq, int nkv, int d, const float *q, 
   // steps per workgroup for this pass's rows (or row groups)
   a.nsub = attention_nsub(units, nkv, max_slots);
   a.nch = attention_chunks(max_slots, a.nsub);
+  a.g = g;
+  a.d_sh = __builtin_ctz(d);
+  a.span_sh = __builtin_ctz(ATT_STEP * a.nsub);
   // chunk index slowest: every row's first chunks are dispatched before any
   // row's later ones, so the last workgroups to start are the short tails
   dim3 g1(nkv, units, a.nch), g2(nq, R);
@@ -721,12 +728,15 @@ void launch_attention(bool bf16, int R, int nq, int nkv, int d, const float *q, 
       if (ntl) hipLaunchKernelGGL((k_attn_mfma<8, true, false>), g1, dim3(256), 0, s, a);
       else hipLaunchKernelGGL((k_attn_mfma<8, false, false>), g1, dim3(256), 0, s, a);
     } else {
-      hipLaunchKernelGGL(k_attn_partial<bf16_t>, g1, dim3(256), 0, s, a);
+      hipLaunchKernelGGL((k_attn_partial<bf16_t, 1>), g1, dim3(256), 0, s, a);   // d = 32
     }
     if (small) hipLaunchKernelGGL(k_attn_combine_w<bf16_t>, g2w, dim3(256), 0, s, a);
     else hipLaunchKernelGGL(k_attn_combine<bf16_t>, g2, dim3(256), 0, s, a);
   } else {
-    hipLaunchKernelGGL(k_attn_partial<float>, g1, dim3(256), 0, s, a);
+    if (d == 32) hipLaunchKernelGGL((k_attn_partial<float, 1>), g1, dim3(256), 0, s, a);
+    else if (d == 64) hipLaunchKernelGGL((k_attn_partial<float, 2>), g1, dim3(256), 0, s, a);
+    else if (d == 128) hipLaunchKernelGGL((k_attn_partial<float, 4>), g1, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_attn_partial<float, 8>), g1, dim3(256), 0, s, a);
     if (small) hipLaunchKernelGGL(k_attn_combine_w<float>, g2w, dim3(256), 0, s, a);
     else hipLaunchKernelGGL(k_attn_combine<float>, g2, dim3(256), 0, s, a);
   }

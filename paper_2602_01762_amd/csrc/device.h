@@ -99,6 +99,34 @@ __device__ __forceinline__ float xor16_f(float v) {
   const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
   return __uint_as_float((threadIdx.x & 16) ? r[0] : r[1]);
 }
+// Sum over aligned groups of 2^sh lanes (sh uniform, 0..6), in every lane of
+// the group: DPP within 16 lanes, permlane swaps above, no LDS.
+__device__ __forceinline__ float group_sum(float v, int sh) {
+  if (sh > 0) v += dpp_f32<DPP_QUAD_XOR1>(v);
+  if (sh > 1) v += dpp_f32<DPP_QUAD_XOR2>(v);
+  if (sh > 2) v += dpp_f32<DPP_HALF_MIRROR>(v);
+  if (sh > 3) v += dpp_f32<DPP_ROW_MIRROR>(v);
+  if (sh > 4) v += xor16_f(v);
+  if (sh > 5) v += xor32_f(v);
+  return v;
+}
+// Sum over the lanes with equal l % stride (a power of two, uniform, 4..64),
+// in each of them: row rotations within 16 lanes, permlane swaps above.
+constexpr int DPP_ROW_ROR4 = 0x124, DPP_ROW_ROR8 = 0x128;
+__device__ __forceinline__ float stride_sum(float v, int stride) {
+  if (stride <= 8) v += dpp_f32<DPP_ROW_ROR8>(v);
+  if (stride <= 4) v += dpp_f32<DPP_ROW_ROR4>(v);
+  if (stride <= 16) v += xor16_f(v);
+  if (stride <= 32) v += xor32_f(v);
+  return v;
+}
+// the wave's index in its workgroup, as a scalar
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+// block and offset of a cache slot
+__device__ __forceinline__ int slot_block(const KvArgs &kv, int t) {
+  return kv.bs_sh >= 0 ? t >> kv.bs_sh : t / kv.bs;
+}
+__device__ __forceinline__ int slot_in_block(const KvArgs &kv, int t, int blk) { return t - blk * kv.bs; }
 // larger value wins; equal values: lower id wins
 __device__ __forceinline__ bool better(float v, int id, float ov, int oid) {
   // bitwise, not short-circuit: lane masks combine without exec-mask branches
@@ -176,7 +204,9 @@ __device__ __forceinline__ void wave_argmax(float &v, int &id) {
   id = key_id(k[0]);
 }
 
-// block-wide (256 threads = 4 waves) reductions through LDS, fixed order
+// block-wide reductions through LDS, fixed order; NW: waves of the workgroup
+// (0: read from the launch, which costs a scalar load)
+template <int NW = 0>
 __device__ __forceinline__ float block_sum(float v, float *sh) {
   v = wave_sum(v);
   const int w = threadIdx.x >> 6;
@@ -184,10 +214,11 @@ __device__ __forceinline__ float block_sum(float v, float *sh) {
   if ((threadIdx.x & 63) == 0) sh[w] = v;
   __syncthreads();
   float t = 0.f;
-  const int nw = blockDim.x >> 6;
+  const int nw = NW ? NW : (int)(blockDim.x >> 6);
   for (int i = 0; i < nw; ++i) t += sh[i];
   return t;
 }
+template <int NW = 0>
 __device__ __forceinline__ float block_max(float v, float *sh) {
   v = wave_max(v);
   const int w = threadIdx.x >> 6;
@@ -195,17 +226,18 @@ __device__ __forceinline__ float block_max(float v, float *sh) {
   if ((threadIdx.x & 63) == 0) sh[w] = v;
   __syncthreads();
   float t = -INFINITY;
-  const int nw = blockDim.x >> 6;
+  const int nw = NW ? NW : (int)(blockDim.x >> 6);
   for (int i = 0; i < nw; ++i) t = fmaxf(t, sh[i]);
   return t;
 }
+template <int NW = 0>
 __device__ __forceinline__ void block_argmax(float &v, int &id, float *shv, int *shi) {
   wave_argmax(v, id);
   const int w = threadIdx.x >> 6;
   __syncthreads();
   if ((threadIdx.x & 63) == 0) { shv[w] = v; shi[w] = id; }
   __syncthreads();
-  const int nw = blockDim.x >> 6;
+  const int nw = NW ? NW : (int)(blockDim.x >> 6);
   v = shv[0];
   id = shi[0];
   for (int i = 1; i < nw; ++i)
@@ -223,20 +255,21 @@ __device__ __forceinline__ void wave_lds_sync() {
 __device__ __forceinline__ float silu(float y) { return y / (1.0f + expf(-y)); }
 
 // Token of row r from the LM head's top-1 partials (larger logit wins, ties
-// -> lower id).  Every thread of the block calls it (block reduction) and
-// gets the result; shv / shi hold one entry per wave.
+// -> lower id).  Every thread of the block (NT threads) calls it (block
+// reduction) and gets the result; shv / shi hold one entry per wave.
 constexpr int TOK_UNROLL = 4;
+template <int NT>
 __device__ __forceinline__ int token_from_lm(const TokFromLm &t, int r, float *shv, int *shi) {
   float bv = -INFINITY;
   int bid = 0x7fffffff;
   const float *pv = t.pval + (size_t)r * t.n_wg;
   const int *pi = t.pid + (size_t)r * t.n_wg;
-  for (int i0 = 0; i0 < t.n_wg; i0 += TOK_UNROLL * (int)blockDim.x) {
+  for (int i0 = 0; i0 < t.n_wg; i0 += TOK_UNROLL * NT) {
     float v[TOK_UNROLL];
     int id[TOK_UNROLL];
 #pragma unroll
     for (int u = 0; u < TOK_UNROLL; ++u) {   // all loads first, then the compares
-      const int i = i0 + u * blockDim.x + threadIdx.x;
+      const int i = i0 + u * NT + threadIdx.x;
       v[u] = i < t.n_wg ? pv[i] : -INFINITY;
       id[u] = i < t.n_wg ? pi[i] : 0x7fffffff;
     }
@@ -244,7 +277,7 @@ __device__ __forceinline__ int token_from_lm(const TokFromLm &t, int r, float *s
     for (int u = 0; u < TOK_UNROLL; ++u)
       if (better(v[u], id[u], bv, bid)) { bv = v[u]; bid = id[u]; }
   }
-  block_argmax(bv, bid, shv, shi);
+  block_argmax<NT / 64>(bv, bid, shv, shi);
   return bid;
 }
 

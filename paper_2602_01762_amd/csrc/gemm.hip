@@ -32,6 +32,11 @@ namespace prism {
 // 32-row gate/up 55.1 -> 51.0 us at 8B and 161.7 -> 151.0 at 70B, 70B LM head
 // 328.6 -> 319.2);
 // fp32 rows are row-major, rows past R read as zero.
+// Lane of a tiled fragment for a lane whose row may lie past R: row 0's piece
+// then, so that few rows fetch few lines.
+__device__ __forceinline__ int frag_lane(int lane, int rt, int R) {
+  return (lane & 15) + 16 * rt < R ? lane : lane & 48;
+}
 template <typename T, int RT, bool PAIR>
 struct BSrc {
   const T *h[RT], *l[RT];
@@ -42,8 +47,8 @@ struct BSrc {
     for (int rt = 0; rt < RT; ++rt) {
       size_t off;
       if constexpr (sizeof(T) == 2) {
-        ok[rt] = true;
-        off = ((size_t)rt * (x.ld / 32) * 64 + lane) * 8;
+        ok[rt] = 16 * rt < R;   // uniform: whole tiles past R are not read
+        off = ((size_t)rt * (x.ld / 32) * 64 + frag_lane(lane, rt, R)) * 8;
       } else {
         const int r = (lane & 15) + 16 * rt;
         ok[rt] = r < R;
@@ -55,19 +60,25 @@ struct BSrc {
   }
   __device__ __forceinline__ u32x4 get(const T *p, bool live, int kb) const {
     constexpr int step = sizeof(T) == 2 ? 512 : Ty<T>::KB;
-    if constexpr (sizeof(T) == 2) return *(const u32x4 *)(p + (size_t)kb * step);
+    // (17 rows or more take 2 row tiles, 33 or more take 4)
+    if constexpr (sizeof(T) == 2 && RT <= 2) return *(const u32x4 *)(p + (size_t)kb * step);
     else return live ? *(const u32x4 *)(p + (size_t)kb * step) : u32x4{0, 0, 0, 0};
   }
   __device__ __forceinline__ u32x4 hi(int rt, int kb) const { return get(h[rt], ok[rt], kb); }
   __device__ __forceinline__ u32x4 lo(int rt, int kb) const { return get(l[rt], ok[rt], kb); }
 };
 
-template <typename T, int RT, int NT, bool PAIR>
+// shadow() runs once, under the loads of the first batch
+struct NoShadow {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <typename T, int RT, int NT, bool PAIR, int UMAX = 8, typename F = NoShadow>
 __device__ __forceinline__ void mainloop(const u32x4 *__restrict__ w0, int nkb, const Act &x,
-                                         int R, int kb0, int kb1, f32x4 (&acc)[NT][RT]) {
+                                         int R, int kb0, int kb1, f32x4 (&acc)[NT][RT],
+                                         F shadow = F()) {
   // k-blocks in flight: about 96 VGPRs of A and B fragments per lane
   constexpr int U0 = 24 / (NT + (PAIR ? 2 : 1) * RT);
-  constexpr int U = U0 > 8 ? 8 : (U0 < 1 ? 1 : U0);
+  constexpr int U = U0 > UMAX ? UMAX : (U0 < 1 ? 1 : U0);
   const int lane = threadIdx.x & 63;
   const BSrc<T, RT, PAIR> bx(x, R);
   const u32x4 *wp[NT];
@@ -91,6 +102,7 @@ __device__ __forceinline__ void mainloop(const u32x4 *__restrict__ w0, int nkb, 
         bh[u][rt] = u < nb ? bx.hi(rt, kb + u) : z4;
         if (PAIR) bl[u][rt] = u < nb ? bx.lo(rt, kb + u) : z4;
       }
+    if (kb == kb0) shadow();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (u < nb) {
@@ -235,8 +247,8 @@ __device__ __forceinline__ void stage_wave(const Act &x, const Gather &gx, const
 // columns per thread step
 template <int RR>
 __device__ __forceinline__ void stage_x(const Act &x, int R, int K, float *xs) {
-  for (int i = threadIdx.x * 8; i < RR * K; i += blockDim.x * 8) {
-    const int r = i / K, k = i % K;
+  for (int i = threadIdx.x * 8; i < RR * K; i += 256 * 8) {   // workgroups of 256 (LM head)
+    const int r = RR == 1 ? 0 : i / K, k = i - r * K;
     float v[8];
     if (r < R) {
       float h[8], l[8];
@@ -327,12 +339,11 @@ __device__ __forceinline__ f32x4 valu_result(float (&acc)[RR]) {
   return f32x4{v[0], v[1], v[2], v[3]};
 }
 
-template <int RR, bool GX>
+template <int RR, bool GX, typename F>
 __device__ __forceinline__ void mainloop_valu(const u32x4 *__restrict__ w0, const Act &x, int R,
                                               int K, float *xs, int kb0, int kb1, f32x4 &out,
-                                              const Gather &gx, uint32_t *err,
-                                              const float *tab = nullptr, int N = 0, int t0 = 0,
-                                              f32x4 *tv = nullptr) {
+                                              const Gather &gx, uint32_t *err, const float *tab,
+                                              int N, int t0, f32x4 *tv, F shadow) {
   const int lane = threadIdx.x & 63, kq = lane >> 4;
   const u32x4 z4 = {0, 0, 0, 0};
   const u32x4 *wp = w0 + (size_t)kb0 * 64 + lane;
@@ -341,7 +352,7 @@ __device__ __forceinline__ void mainloop_valu(const u32x4 *__restrict__ w0, cons
   // ahead of the weights, so that the argmax does not wait for them.  With
   // the embedding table (tab), wave 0 resolves them for the epilogue and
   // requests its tile's table values right after its first weight batch.
-  const bool tab_wave = GX && tab != nullptr && (threadIdx.x >> 6) == 0;
+  const bool tab_wave = GX && tab != nullptr && wave_id() == 0;
   const bool need_tok = GX && ((kb1 > kb0 && kb0 * 32 < gx.H) || tab_wave);
   const bool from_lm = need_tok && gx.lm.pval;
   constexpr int PRE = RR == 1 ? 8 : 2;   // entries per lane issued early (registers)
@@ -385,6 +396,7 @@ __device__ __forceinline__ void mainloop_valu(const u32x4 *__restrict__ w0, cons
                           : f32x4{0.f, 0.f, 0.f, 0.f};
   }
   stage_wave<RR, GX>(x, gx, tok, R, K, xs, kb0 * 32, kb1 * 32);
+  shadow();
   wave_lds_sync();
   float acc[RR];
 #pragma unroll
@@ -475,10 +487,10 @@ __device__ __forceinline__ void put_act(const ActOut &o, int r, int c, float v) 
 }
 
 // Row scales 1/sqrt(mean(x^2) + eps) of rows r0 .. r0 + nr - 1 from the
-// producer's partial sums of squares (layout [part][R]).  Thread t serves row
-// r0 + t / tpr and adds parts t % tpr, t % tpr + tpr, ... in that order; the
-// tpr threads of a row (adjacent lanes of one wave) then meet in a fixed
-// butterfly, so the result does not depend on scheduling.  The first
+// producer's partial sums of squares (layout [part][R]).  The 2^tsh threads
+// of a row are adjacent lanes of one wave; thread t of them adds parts t,
+// t + 2^tsh, ... in that order and they meet in a fixed butterfly, so the
+// result does not depend on scheduling.  The first
 // SS_PER_THREAD parts of each thread are requested before the main loop
 // (issue_scales); finish_scales adds them and loads any further ones (up to
 // SS_MAX_ROUNDS times as many) after it.
@@ -487,90 +499,163 @@ constexpr int SS_MAX_ROUNDS = 4;
 struct ScaleLoads {
   float v[SS_PER_THREAD];
 };
-__host__ __device__ inline int scale_tpr(int threads, int nr) {
-  int t = 64;
-  while (t > 1 && t * nr > threads) t >>= 1;
-  return t;
+// log2 of the threads per row: a power of two up to a wave
+static int scale_tsh(int threads, int nr) {
+  int sh = 6;
+  while (sh > 0 && (nr << sh) > threads) --sh;
+  return sh;
 }
-__host__ __device__ inline bool scales_fit(int threads, int nr, int n_parts) {
-  return nr <= threads && n_parts <= SS_MAX_ROUNDS * SS_PER_THREAD * scale_tpr(threads, nr);
+static bool scales_fit(int threads, int nr, int n_parts) {
+  return nr <= threads && n_parts <= (SS_MAX_ROUNDS * SS_PER_THREAD << scale_tsh(threads, nr));
 }
 __device__ __forceinline__ ScaleLoads issue_scales(const RowNorm &nm, int R, int r0, int nr) {
   ScaleLoads s;
-  const int tpr = scale_tpr(blockDim.x, nr);
-  const int r = threadIdx.x / tpr, sub = threadIdx.x % tpr;
+  const int r = threadIdx.x >> nm.tsh, sub = threadIdx.x & ((1 << nm.tsh) - 1);
 #pragma unroll
   for (int j = 0; j < SS_PER_THREAD; ++j) {
-    const int p = sub + j * tpr;
-    s.v[j] = r < nr && p < nm.n_parts ? nm.ss[(size_t)p * R + r0 + r] : 0.f;
+    const int p = sub + (j << nm.tsh);
+    s.v[j] = 0.f;
+    if ((j << nm.tsh) < nm.n_parts)   // uniform; the load itself is clamped and masked
+      s.v[j] = nm.ss[(size_t)min(p, nm.n_parts - 1) * R + r0 + min(r, nr - 1)];
+    s.v[j] = r < nr && p < nm.n_parts ? s.v[j] : 0.f;
   }
   return s;
 }
 // every thread of the block calls it (barrier); rowscale[0 .. nr - 1]
 __device__ __forceinline__ void finish_scales(const RowNorm &nm, int R, int r0, int nr,
                                               const ScaleLoads &s, float *rowscale) {
-  const int tpr = scale_tpr(blockDim.x, nr);
+  const int r = threadIdx.x >> nm.tsh, sub = threadIdx.x & ((1 << nm.tsh) - 1);
   float acc = 0.f;
 #pragma unroll
   for (int j = 0; j < SS_PER_THREAD; ++j) acc += s.v[j];
-  {
-    const int r = threadIdx.x / tpr;
-    for (int p = threadIdx.x % tpr + SS_PER_THREAD * tpr; r < nr && p < nm.n_parts; p += tpr)
-      acc += nm.ss[(size_t)p * R + r0 + r];
-  }
-  for (int o = 1; o < tpr; o <<= 1) acc += __shfl_xor(acc, o, 64);
-  const int r = threadIdx.x / tpr;
-  if (r < nr && threadIdx.x % tpr == 0) rowscale[r] = 1.0f / sqrtf(acc / (float)nm.n + nm.eps);
+  for (int p0 = SS_PER_THREAD << nm.tsh; p0 < nm.n_parts; p0 += 1 << nm.tsh)
+    if (r < nr && p0 + sub < nm.n_parts) acc += nm.ss[(size_t)(p0 + sub) * R + r0 + r];
+  acc = group_sum(acc, nm.tsh);
+  if (r < nr && sub == 0) rowscale[r] = 1.0f / sqrtf(acc / (float)nm.n + nm.eps);
   __syncthreads();
 }
 
+// k-blocks [k0, k1) of part i (a wave's or a slice's)
+__device__ __forceinline__ void k_range(const GemmLaunch &g, int i, int &k0, int &k1) {
+  k0 = g.kb_lo + i * g.kq + min(i, g.kr);
+  k1 = k0 + g.kq + (i < g.kr ? 1 : 0);
+}
+// what the kernels would have to divide for: parts of the k range, log2 d
+static GemmLaunch with_counts(GemmLaunch g, int parts) {
+  const int nk = g.kb_n ? g.kb_n : g.m.nkb - g.kb_lo;
+  g.kq = nk / parts;
+  g.kr = nk % parts;
+  g.d_sh = g.d > 0 ? __builtin_ctz(g.d) : 0;
+  return g;
+}
+
+// Rotation of a lane's 4 dims at a position, in fp64: the angle less its
+// nearest multiple of pi/2, the Taylor sums of sine and cosine on what is
+// left (|r| <= pi/4: the terms dropped are below 1e-11), and the quadrant.
+// No branch and no scratch (the library's sincosf keeps a large-argument
+// path), but still a few hundred cycles of one wave, so the kernels compute
+// it while their first loads are in flight.
+struct Rot {
+  float c[4], s[4];
+};
+__device__ __forceinline__ Rot rotation(int pos, const double (&freq)[4]) {
+  Rot t;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const double ang = (double)pos * freq[i];
+    const double q = rint(ang * 0.63661977236758134);           // 2 / pi
+    double r = fma(-q, 1.5707963267948966, ang);                 // pi / 2, high and low words
+    r = fma(-q, 6.123233995736766e-17, r);
+    const double z = r * r;
+    double sn = fma(z, -1.0 / 39916800.0, 1.0 / 362880.0);
+    sn = fma(z, sn, -1.0 / 5040.0);
+    sn = fma(z, sn, 1.0 / 120.0);
+    sn = fma(z, sn, -1.0 / 6.0);
+    sn = fma(z * r, sn, r);
+    double cs = fma(z, 1.0 / 479001600.0, -1.0 / 3628800.0);
+    cs = fma(z, cs, 1.0 / 40320.0);
+    cs = fma(z, cs, -1.0 / 720.0);
+    cs = fma(z, cs, 1.0 / 24.0);
+    cs = fma(z, cs, -0.5);
+    cs = fma(z, cs, 1.0);
+    const int quad = (int)q & 3;
+    const float fs = (float)((quad & 1) ? cs : sn), fc = (float)((quad & 1) ? sn : cs);
+    t.s[i] = (quad & 2) ? -fs : fs;
+    t.c[i] = ((quad + 1) & 2) ? -fc : fc;
+  }
+  return t;
+}
+
 // Operands of one lane's epilogue that do not depend on the product: the
-// residual and gain values (EPI_NORM) or the RoPE inverse frequencies
-// (EPI_QKV) of its 4 outputs.  The finish pass loads them before the slice
-// sums, so that they do not add a round trip after them.
+// residual and gain values (EPI_NORM), or the cache slot and the rotation of
+// its 4 outputs (EPI_QKV).  Their loads go out around the first weight (or
+// slice) loads, and the rotation is computed under those, so that neither
+// adds a round trip after the stream.
 struct EpiPre {
   f32x4 res;
   float gain[4];
-  float freq[4];
+  double freq[4];
+  int pos, seq, slot;
+  long cbase;    // cache slot (block, head 0, offset) of the row, or -1
+  Rot rot;
 };
 
+// the loads that depend on nothing
 template <typename T, int EPI>
-__device__ __forceinline__ EpiPre epilogue_prefetch(const GemmLaunch &g, int tile, int r) {
+__device__ __forceinline__ EpiPre epilogue_issue(const GemmLaunch &g, int tile, int r) {
   const int n0 = tile * 16 + 4 * ((threadIdx.x & 63) >> 4);
   EpiPre p;
   p.res = f32x4{0.f, 0.f, 0.f, 0.f};
+  p.cbase = -1;
+  p.pos = p.seq = p.slot = -1;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) p.gain[i] = p.freq[i] = 0.f;
+  for (int i = 0; i < 4; ++i) {
+    p.gain[i] = 0.f;
+    p.freq[i] = 0.;
+  }
   if (r >= g.R) return p;
   if (EPI == EPI_NORM) {
     if (g.res) p.res = *(const f32x4 *)(g.res + (size_t)r * g.ldres + n0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) p.gain[i] = Ty<T>::ld((const T *)g.gain, n0 + i);
   } else if (EPI == EPI_QKV) {
-    const int f0 = (g.tile0 + tile) * 16, d = g.d;
-    const int qd = g.nq * d, kd = g.nkv * d;
-    if (f0 < qd + kd) {
-      const int fr = f0 < qd ? f0 : f0 - qd;
-      const int dim0 = 8 * ((fr % d) / 16) + 4 * ((threadIdx.x & 63) >> 4 & 1);
+    p.pos = g.rows.pos[r];
+    p.seq = g.rows.seq[r];
+    p.slot = g.rows.slot[r];
+    const int f0 = (g.tile0 + tile) * 16, qd = g.nq << g.d_sh;
+    const int fr = f0 < qd ? f0 : f0 - qd;
+    // (v rows rotate nothing: their lanes load and compute it all the same)
+    const int dim0 = (((fr & (g.d - 1)) >> 4) << 3) + 4 * ((threadIdx.x & 63) >> 4 & 1);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) p.freq[i] = g.inv_freq[dim0 + i];
-    }
+    for (int i = 0; i < 4; ++i) p.freq[i] = g.inv_freq[dim0 + i];
   }
   return p;
+}
+
+// what follows from them (EPI_QKV), to be called under other loads
+template <int EPI>
+__device__ __forceinline__ void epilogue_shadow(const GemmLaunch &g, EpiPre &p) {
+  if constexpr (EPI == EPI_QKV) {
+    const int bi = slot_block(g.kv, p.slot);
+    if (p.seq >= 0 && p.seq < g.kv.n_seq && p.slot >= 0 && bi < g.kv.mbps) {
+      const int blk = g.kv.block_table[(size_t)p.seq * g.kv.mbps + bi];
+      if (blk >= 0 && blk < g.kv.n_blocks)
+        p.cbase = (((long)blk * g.nkv * g.kv.bs) << g.d_sh) + ((long)slot_in_block(g.kv, p.slot, bi) << g.d_sh);
+    }
+    p.rot = rotation(p.pos, p.freq);
+  }
 }
 
 // Epilogue of one 16x16 accumulator tile in the MFMA layout: the lane holds
 // output rows n0..n0+3 (tiled order) of batch row r = (lane & 15) + 16 rt.
 // Every lane of the wave must call it (it shuffles).  scale: the row's
-// RMSNorm scale (1 if none); cbase / rpos: the row's cache slot and position
-// (QKV only); pre: the lane's prefetched operands (else loaded here).
+// RMSNorm scale (1 if none); pre: the lane's prefetched operands (needed for
+// EPI_QKV; EPI_NORM loads them here without it).
 // EPI_NORM returns the tile's sum of squares of row r (valid in lanes
 // 0..15); the caller stores it.
 template <typename T, int EPI>
 __device__ __forceinline__ float epilogue_tile(const GemmLaunch &g, int tile, int r, f32x4 a,
-                                               float scale, long cbase, int rpos,
-                                               f32x4 tadd = f32x4{0.f, 0.f, 0.f, 0.f},
-                                               const EpiPre *pre = nullptr) {
+                                               float scale, f32x4 tadd, const EpiPre *pre) {
   const int lane = threadIdx.x & 63, q4 = lane >> 4;
   const int n0 = tile * 16 + 4 * q4;
   const bool live = r < g.R;
@@ -608,8 +693,9 @@ __device__ __forceinline__ float epilogue_tile(const GemmLaunch &g, int tile, in
     }
   } else {  // EPI_QKV
     const int d = g.d, half = d >> 1;
-    const int qd = g.nq * d, kd = g.nkv * d;
+    const int qd = g.nq << g.d_sh, kd = g.nkv << g.d_sh;
     const int f0 = (g.tile0 + tile) * 16;   // first feature of the tile (tiled order)
+    const long cbase = pre->cbase;
     // partner values for the rotation (lanes l and l ^ 32 hold the two halves)
     float pv[4];
 #pragma unroll
@@ -618,19 +704,15 @@ __device__ __forceinline__ float epilogue_tile(const GemmLaunch &g, int tile, in
     if (f0 < qd + kd) {
       const bool isq = f0 < qd;
       const int fr = isq ? f0 : f0 - qd;
-      const int head = fr / d;
-      const int j = (fr % d) / 16;       // tile index within the head
+      const int head = fr >> g.d_sh;
+      const int j = (fr & (d - 1)) >> 4;       // tile index within the head
       const bool first = q4 < 2;
       const int dim0 = 8 * j + 4 * (q4 & 1);   // dim within the first half
       float out[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        // angle in fp64, reduced to [-pi, pi] in fp64, cos/sin in fp32
-        const double ang = (double)rpos * (pre ? pre->freq[i] : g.inv_freq[dim0 + i]);
-        const double red = ang - 6.283185307179586 * rint(ang * 0.15915494309189535);
-        float sn, cs;
-        sincosf((float)red, &sn, &cs);
         // first half: y1 = x1 c - x2 s ; second half: y2 = x2 c + x1 s
+        const float cs = pre->rot.c[i], sn = pre->rot.s[i];
         out[i] = first ? v[i] * cs - pv[i] * sn : v[i] * cs + pv[i] * sn;
       }
       const int dimb = first ? dim0 : half + dim0;
@@ -648,8 +730,8 @@ __device__ __forceinline__ float epilogue_tile(const GemmLaunch &g, int tile, in
       }
     } else {
       const int fr = f0 - qd - kd;
-      const int head = fr / d;
-      const int dim = fr % d + 4 * q4;
+      const int head = fr >> g.d_sh;
+      const int dim = (fr & (d - 1)) + 4 * q4;
       const long base = cbase < 0 ? -1 : cbase + (long)head * g.kv.bs * d;
       if (base < 0) {
         atomicOr(g.err, ERRF_CAPACITY);
@@ -660,19 +742,6 @@ __device__ __forceinline__ float epilogue_tile(const GemmLaunch &g, int tile, in
     }
   }
   return 0.f;
-}
-
-// cache slot (block, head 0, offset) and position of row r, or -1
-__device__ __forceinline__ long cache_base(const GemmLaunch &g, int r, int &pos) {
-  pos = g.rows.pos[r];
-  const int b = g.rows.seq[r], slot = g.rows.slot[r];
-  const int bi = slot / g.kv.bs;
-  if (b >= 0 && b < g.kv.n_seq && slot >= 0 && bi < g.kv.mbps) {
-    const int blk = g.kv.block_table[(size_t)b * g.kv.mbps + bi];
-    if (blk >= 0 && blk < g.kv.n_blocks)
-      return (long)blk * g.nkv * g.kv.bs * g.d + (long)(slot % g.kv.bs) * g.d;
-  }
-  return -1;
 }
 
 // batched variants (more accumulators) run at most 8 waves per workgroup,
@@ -694,44 +763,38 @@ __global__ __launch_bounds__((gemm_max_threads<RT, NT>())) void k_gemm(GemmLaunc
   // then (GEMV path, VR > 0) VR * K floats of staged activations
   extern __shared__ f32x4 red[];
   __shared__ float rowscale[MAX_ROWS];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = wave_id(), lane = threadIdx.x & 63;
   const int kw = g.kw;
   const int t0 = blockIdx.x * NT;
   const TiledMat &m = g.m;
   const bool has_norm = !GX && (g.norm.scale != nullptr || g.norm.n_parts > 0);
   const bool own_scales = !GX && g.norm.scale == nullptr && g.norm.n_parts > 0;
+  constexpr int NP = NT * RT;
+  // one tile: wave 0 prefetches its epilogue's operands
+  EpiPre pre;
+  const bool lead = NP == 1 && wave == 0;
+  if (EPI == EPI_QKV && lead) pre = epilogue_issue<T, EPI>(g, t0, lane & 15);
   ScaleLoads sl;
   if (own_scales) sl = issue_scales(g.norm, g.R, 0, g.R);
-
-  // QKV: wave 0 looks up its rows' cache slots and positions before the
-  // main loop, so these dependent loads overlap the weight stream
-  long cbase[RT];
-  int rpos[RT];
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    cbase[rt] = -1;
-    rpos[rt] = 0;
-  }
-  if constexpr (EPI == EPI_QKV) {
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const int r = (lane & 15) + 16 * rt;
-      if (wave == 0 && r < g.R) cbase[rt] = cache_base(g, r, rpos[rt]);
+  auto shadow = [&]() {
+    if constexpr (NP == 1) {
+      if (!lead) return;
+      if (EPI == EPI_NORM) pre = epilogue_issue<T, EPI>(g, t0, lane & 15);
+      epilogue_shadow<EPI>(g, pre);
     }
-  }
+  };
   f32x4 acc[NT][RT];
   f32x4 tv = f32x4{0.f, 0.f, 0.f, 0.f};   // GEMV fusion FC: wave 0's embedding-table values
 #pragma unroll
   for (int n = 0; n < NT; ++n)
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) acc[n][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int nk = m.nkb - g.kb_lo;
-  const int kb0 = g.kb_lo + (int)((long)wave * nk / kw);
-  const int kb1 = g.kb_lo + (int)((long)(wave + 1) * nk / kw);
+  int kb0, kb1;
+  k_range(g, wave, kb0, kb1);
   if constexpr (VR > 0) {
     float *xs = (float *)&red[(kw - 1) * NT * RT * 64] + 64 * kw;
     mainloop_valu<VR, GX>((const u32x4 *)m.w + (size_t)t0 * m.nkb * 64, g.x, g.R, m.K, xs, kb0,
-                          kb1, acc[0][0], g.gx, g.err, g.tab, m.N, t0, &tv);
+                          kb1, acc[0][0], g.gx, g.err, g.tab, m.N, t0, &tv, shadow);
   } else {
     // up to 16 rows (7 or more tiles: registers) the next batch of k-blocks
     // is in flight while one is consumed: batch 16 -0.7%; at 32 rows the
@@ -739,15 +802,14 @@ __global__ __launch_bounds__((gemm_max_threads<RT, NT>())) void k_gemm(GemmLaunc
     if constexpr (RT == 1 && NT >= 7 && sizeof(T) == 2)
       mainloop_db<T, RT, NT, PAIR>((const u32x4 *)m.w + (size_t)t0 * m.nkb * 64, m.nkb, g.x, g.R,
                                    kb0, kb1, acc);
-    else
-      mainloop<T, RT, NT, PAIR>((const u32x4 *)m.w + (size_t)t0 * m.nkb * 64, m.nkb, g.x, g.R, kb0,
-                                kb1, acc);
+    else   // (one tile: the rotation's registers beside 4 k-blocks)
+      mainloop<T, RT, NT, PAIR, NP == 1 && EPI == EPI_QKV ? 4 : 8>(
+          (const u32x4 *)m.w + (size_t)t0 * m.nkb * 64, m.nkb, g.x, g.R, kb0, kb1, acc, shadow);
   }
   // Several accumulator tiles (batched unsplit products): every wave leaves
   // its sums in LDS and takes every kw-th tile through the reduction and the
   // epilogue (wave 0 alone did both, after the weight stream had ended).  The
   // sums are added in wave order either way.
-  constexpr int NP = NT * RT;
   const bool share = NP > 1 && kw > 1;
   if (kw > 1 && (share || wave > 0)) {
 #pragma unroll
@@ -762,7 +824,7 @@ __global__ __launch_bounds__((gemm_max_threads<RT, NT>())) void k_gemm(GemmLaunc
   } else if (kw > 1) {
     __syncthreads();
   }
-  auto finish = [&](int n, int rt, f32x4 a, long cb, int rp) {
+  auto finish = [&](int n, int rt, f32x4 a) {
     const int r = (lane & 15) + 16 * rt;
     const float sc = has_norm && r < g.R ? (own_scales ? rowscale[r] : g.norm.scale[r]) : 1.f;
     f32x4 tadd = GX ? tv : f32x4{0.f, 0.f, 0.f, 0.f};
@@ -770,7 +832,12 @@ __global__ __launch_bounds__((gemm_max_threads<RT, NT>())) void k_gemm(GemmLaunc
       const int t = g.tab_tok[r];
       if (t >= 0) tadd = *(const f32x4 *)(g.tab + (size_t)t * m.N + (t0 + n) * 16 + 4 * (lane >> 4));
     }
-    const float ss = epilogue_tile<T, EPI>(g, t0 + n, r, a, sc, cb, rp, tadd);
+    if constexpr (NP > 1 && EPI == EPI_QKV) {
+      pre = epilogue_issue<T, EPI>(g, t0 + n, r);
+      epilogue_shadow<EPI>(g, pre);
+    }
+    const float ss = epilogue_tile<T, EPI>(g, t0 + n, r, a, sc, tadd,
+                                           NP == 1 || EPI == EPI_QKV ? &pre : nullptr);
     if (EPI == EPI_NORM && r < g.R && lane < 16) g.ss[(size_t)(t0 + n) * g.R + r] = ss;
   };
   if constexpr (NP > 1) {
@@ -778,7 +845,7 @@ __global__ __launch_bounds__((gemm_max_threads<RT, NT>())) void k_gemm(GemmLaunc
       for (int p = wave; p < NP; p += kw) {
         f32x4 a = red[p * 64 + lane];
         for (int j = 1; j < kw; ++j) a += red[(j * NP + p) * 64 + lane];
-        finish(p / RT, p % RT, a, cbase[0], rpos[0]);   // (QKV: one tile, below)
+        finish(p / RT, p % RT, a);
       }
       return;
     }
@@ -792,7 +859,7 @@ __global__ __launch_bounds__((gemm_max_threads<RT, NT>())) void k_gemm(GemmLaunc
 #pragma unroll
   for (int n = 0; n < NT; ++n)
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) finish(n, rt, acc[n][rt], cbase[rt], rpos[rt]);
+    for (int rt = 0; rt < RT; ++rt) finish(n, rt, acc[n][rt]);
 }
 
 // Token of row i for a K-split fusion FC that has no prep pass: wave 0 of
@@ -807,8 +874,8 @@ struct SplitTok {
 };
 __device__ __forceinline__ SplitTok split_tok_issue(const GemmLaunch &g) {
   SplitTok st;
-  const int i = blockIdx.y * gridDim.x + blockIdx.x;
-  if (!g.tok_out || (threadIdx.x >> 6) != 0 || i >= g.R) return st;
+  const int i = blockIdx.y * g.nwg_x + blockIdx.x;
+  if (!g.tok_out || wave_id() != 0 || i >= g.R) return st;
   st.row = i;
   if (g.gx.lm.pval) st.l = issue_tok<SPLIT_TOK_PRE>(g.gx.lm, i);
   else st.tok = g.gx.in.tokens[i];
@@ -836,16 +903,16 @@ __device__ __forceinline__ void split_tok_store(const GemmLaunch &g, const Split
 // order and applies the epilogue.
 template <typename T, int RT, int NT, bool PAIR>
 __global__ __launch_bounds__(256) void k_gemm_split(GemmLaunch g) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = wave_id(), lane = threadIdx.x & 63;
   const TiledMat &m = g.m;
   const int t0 = (blockIdx.x * 4 + wave) * NT;
   if (t0 >= m.n_tiles) return;   // n_tiles is a multiple of NT; no barriers below
   // (resolved before the main loop: kept across it, its registers lowered
   // the occupancy of some instantiations)
   split_tok_store(g, split_tok_issue(g));   // wave 0 is never idle
-  const int S = gridDim.y, sl = blockIdx.y;
-  const int nk = m.nkb - g.kb_lo;
-  const int kb0 = g.kb_lo + (int)((long)sl * nk / S), kb1 = g.kb_lo + (int)((long)(sl + 1) * nk / S);
+  const int sl = blockIdx.y;
+  int kb0, kb1;
+  k_range(g, sl, kb0, kb1);
   f32x4 acc[NT][RT];
 #pragma unroll
   for (int n = 0; n < NT; ++n)
@@ -885,13 +952,13 @@ __global__ __launch_bounds__(256) void k_gemm_split_lds(GemmLaunch g) {
   extern __shared__ u32x4 xs_split[];    // [nf][64]
   constexpr int SF = SPLIT_LDS_FRAGS / 4;  // fragments per wave
   constexpr int U = 16 / NT > 0 ? 16 / NT : 1;   // k-blocks per batch
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = wave_id(), lane = threadIdx.x & 63;
   const TiledMat &m = g.m;
   const int t0 = (blockIdx.x * 4 + wave) * NT;
   const bool live = t0 < m.n_tiles;       // n_tiles is a multiple of NT
-  const int S = gridDim.y, sl = blockIdx.y;
-  const int nk = m.nkb - g.kb_lo;
-  const int kb0 = g.kb_lo + (int)((long)sl * nk / S), kb1 = g.kb_lo + (int)((long)(sl + 1) * nk / S);
+  const int sl = blockIdx.y;
+  int kb0, kb1;
+  k_range(g, sl, kb0, kb1);
   const int nf = (kb1 - kb0) * 2 * RT;    // <= SPLIT_LDS_FRAGS (checked by the launcher)
   const SplitTok stok = split_tok_issue(g);   // wave 0 is live in every workgroup
   // staging loads: fragment f = (k-block i, plane p, row tile rt) as it is
@@ -903,7 +970,8 @@ __global__ __launch_bounds__(256) void k_gemm_split_lds(GemmLaunch g) {
     const int f = max(min(wave + 4 * i, nf - 1), 0);
     const int kbi = f / (2 * RT), pl = (f / RT) & 1, rt = f % RT;
     const int kb = min(kb0 + kbi, m.nkb - 1);
-    sv[i] = ((const u32x4 *)(pl ? g.x.lo : g.x.hi))[((size_t)rt * (g.x.ld / 32) + kb) * 64 + lane];
+    sv[i] = ((const u32x4 *)(pl ? g.x.lo : g.x.hi))[((size_t)rt * (g.x.ld / 32) + kb) * 64 +
+                                                    frag_lane(lane, rt, g.R)];
   }
   const u32x4 *wp[NT];
 #pragma unroll
@@ -980,7 +1048,7 @@ static int finish_tiles(int n_tiles, int epi) {
   return f;
 }
 
-// One wave per (tile, 16-row group), FT = blockDim.x / 64 consecutive tiles
+// One wave per (tile, 16-row group), FT = g.kw consecutive tiles
 // per workgroup: the slices' partial sums in slice order, then the shared
 // epilogue.  The row scales of a normed operand (QKV, SWIGLU) are reduced
 // here from the producer's partials (or come precomputed).  EPI_NORM sums of
@@ -991,8 +1059,8 @@ template <typename T, int EPI>
 __global__ __launch_bounds__(512) void k_gemm_finish(GemmLaunch g) {
   __shared__ float rowscale[16];
   __shared__ float ssw[8][16];    // [wave][row of the group]
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int ft = blockDim.x >> 6;
+  const int wave = wave_id(), lane = threadIdx.x & 63;
+  const int ft = g.kw;                   // tiles, and waves, per workgroup
   const int tile = blockIdx.x * ft + wave;
   const int r0 = 16 * blockIdx.y, nr = min(16, g.R - r0);
   const int r = (lane & 15) + r0;
@@ -1002,12 +1070,9 @@ __global__ __launch_bounds__(512) void k_gemm_finish(GemmLaunch g) {
   const int n0 = tile * 16 + 4 * (lane >> 4);
   f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
   f32x4 tadd = f32x4{0.f, 0.f, 0.f, 0.f};   // fusion FC: the row's embedding-table term
-  long cbase = -1;
-  int rpos = 0;
   // operands that do not depend on the slices go out before them
-  const EpiPre pre = epilogue_prefetch<T, EPI>(g, tile, r);
+  EpiPre pre = epilogue_issue<T, EPI>(g, tile, r);
   if (r < g.R) {
-    if (EPI == EPI_QKV) cbase = cache_base(g, r, rpos);
     // the row's token goes out first, its table row right after the first
     // batch of slice loads, so the two dependent loads overlap the slices
     const bool tab = EPI == EPI_NORM && g.tab;
@@ -1025,7 +1090,10 @@ __global__ __launch_bounds__(512) void k_gemm_finish(GemmLaunch g) {
 #pragma unroll
       for (int j = 0; j < FIN_UNROLL; ++j)
         v[j] = s0 + j < g.split ? pp[(size_t)(s0 + j) * stride] : f32x4{0.f, 0.f, 0.f, 0.f};
-      if (s0 == 0 && ttok >= 0) tadd = *(const f32x4 *)(g.tab + (size_t)ttok * g.m.N + n0);
+      if (s0 == 0) {
+        if (ttok >= 0) tadd = *(const f32x4 *)(g.tab + (size_t)ttok * g.m.N + n0);
+        epilogue_shadow<EPI>(g, pre);
+      }
 #pragma unroll
       for (int j = 0; j < FIN_UNROLL; ++j)
         if (s0 + j < g.split) a += v[j];
@@ -1038,7 +1106,7 @@ __global__ __launch_bounds__(512) void k_gemm_finish(GemmLaunch g) {
   } else if (g.norm.scale && r < g.R) {
     sc = g.norm.scale[r];
   }
-  const float ss = epilogue_tile<T, EPI>(g, tile, r, a, sc, cbase, rpos, tadd, &pre);
+  const float ss = epilogue_tile<T, EPI>(g, tile, r, a, sc, tadd, &pre);
   if constexpr (EPI == EPI_NORM) {
     if (lane < 16) ssw[wave][lane] = ss;
     __syncthreads();
@@ -1064,7 +1132,7 @@ __global__ __launch_bounds__(256) void k_lmhead(LmLaunch g) {
   __shared__ float sl[RT * 16][64 * NT + 1];
   __shared__ float rowscale[MAX_ROWS];
   const TiledMat &m = g.m;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = wave_id(), lane = threadIdx.x & 63;
   const int t0 = (blockIdx.x * 4 + wave) * NT;
   const bool has_norm = g.norm.scale != nullptr || g.norm.n_parts > 0;
   const bool own_scales = g.norm.scale == nullptr && g.norm.n_parts > 0;
@@ -1211,10 +1279,11 @@ __global__ __launch_bounds__(256) void k_lmhead(LmLaunch g) {
 static_assert(GEMV_MAX_ROWS == 2, "GEMV variants cover 1 and 2 rows");
 
 template <typename T, int RT, int NT, bool PAIR, int VR>
-static bool gemm_epi(const GemmLaunch &g, hipStream_t s) {
-  if (g.kw < 1 || 64 * g.kw > gemm_max_threads<RT, NT>()) return false;
+static bool gemm_epi(const GemmLaunch &gl, hipStream_t s) {
+  if (gl.kw < 1 || 64 * gl.kw > gemm_max_threads<RT, NT>()) return false;
+  GemmLaunch g = with_counts(gl, gl.kw);
+  g.norm.tsh = scale_tsh(64 * g.kw, g.R);
   dim3 grid(g.m.n_tiles / NT);
-  if (NT * RT > 1 && g.kw > 1 && g.epi == EPI_QKV) return false;   // its rows' slots are wave 0's
   const int parts = NT * RT > 1 && g.kw > 1 ? g.kw : g.kw - 1;     // partial sums kept per tile
   size_t lds = (size_t)(parts * NT * RT * 64) * sizeof(f32x4) +
                (size_t)64 * g.kw * sizeof(float);
@@ -1393,15 +1462,14 @@ void k_gemm_tile(GemmLaunch g) {
   extern __shared__ u32x4 xs_tile[];
   const TiledMat &m = g.m;
   const int mt = (m.n_tiles + S::FM - 1) / S::FM, rt = (g.R + 16 * S::FN - 1) / (16 * S::FN);
-  const int per = (int)(gridDim.x >> 3), L = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  const int per = g.nwg_x >> 3, L = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
   if (L >= mt * rt * g.split) return;        // padding workgroup (uniform)
   const int sl = L / (mt * rt), in = L % (mt * rt);
   const int sg = in / (4 * mt), rs = min(4, rt - 4 * sg), w = in - sg * 4 * mt;
   const int m0 = w / rs * S::FM, r0 = (sg * 4 + w % rs) * 16 * S::FN;
-  const int nk = g.kb_n ? g.kb_n : m.nkb - g.kb_lo;
   // split <= nk (host check): every slice has at least one k-block
-  const int kb0 = g.kb_lo + (int)((long)sl * nk / g.split);
-  const int kb1 = g.kb_lo + (int)((long)(sl + 1) * nk / g.split);
+  int kb0, kb1;
+  k_range(g, sl, kb0, kb1);
   f32x4 acc[S::TM][S::TN];
   tile_loop<S>(m, m0, g.x, g.R, r0, kb0, kb1, g.kb_lo, xs_tile, acc);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q4 = lane >> 4;
@@ -1419,7 +1487,7 @@ void k_gemm_tile(GemmLaunch g) {
       if constexpr (EPI == EPI_NORM) {           // slice partials for the finish pass
         *(f32x4 *)(g.part + ((size_t)sl * g.R + r) * m.N + t * 16 + 4 * q4) = v;
       } else if constexpr (EPI == EPI_SWIGLU) {  // z = SiLU(gate) * up; no shuffles
-        (void)epilogue_tile<bf16_t, EPI_SWIGLU>(g, t, r, v, sc, -1, 0);
+        (void)epilogue_tile<bf16_t, EPI_SWIGLU>(g, t, r, v, sc, f32x4{0.f, 0.f, 0.f, 0.f}, nullptr);
       } else {                                   // EPI_STORE: y[r][n] = scale[r] acc
         *(f32x4 *)(g.y + (size_t)r * g.ldy + t * 16 + 4 * q4) =
             f32x4{v.x * sc, v.y * sc, v.z * sc, v.w * sc};
@@ -1429,18 +1497,23 @@ void k_gemm_tile(GemmLaunch g) {
 }
 
 template <typename S, int EPI>
-static void tile_launch(const GemmLaunch &g, hipStream_t s) {
+static void tile_launch(const GemmLaunch &gl, hipStream_t s) {
+  GemmLaunch g = with_counts(gl, gl.split);
   // more than 64 KiB of dynamic LDS has to be allowed, on each device
   (void)hipFuncSetAttribute((const void *)k_gemm_tile<S, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)S::LDS);
   const long wgs = (long)((g.m.n_tiles + S::FM - 1) / S::FM) * ((g.R + 16 * S::FN - 1) / (16 * S::FN)) * g.split;
-  hipLaunchKernelGGL((k_gemm_tile<S, EPI>), dim3((unsigned)((wgs + 7) / 8 * 8)), dim3(64 * S::NW), S::LDS, s, g);
+  g.nwg_x = (int)((wgs + 7) / 8 * 8);
+  hipLaunchKernelGGL((k_gemm_tile<S, EPI>), dim3(g.nwg_x), dim3(64 * S::NW), S::LDS, s, g);
 }
 
 // the finish pass of a K-split product: one wave per (tile, 16 rows)
 template <typename T>
-static void finish_launch(const GemmLaunch &g, hipStream_t s) {
+static void finish_launch(const GemmLaunch &gl, hipStream_t s) {
+  GemmLaunch g = with_counts(gl, 1);
   const int ft = finish_tiles(g.m.n_tiles, g.epi);
+  g.kw = ft;
+  g.norm.tsh = scale_tsh(64 * ft, g.R < 16 ? g.R : 16);   // the last row group may be smaller
   const dim3 fg(g.m.n_tiles / ft, (g.R + 15) / 16), fb(64 * ft);
   if (g.epi == EPI_NORM) hipLaunchKernelGGL((k_gemm_finish<T, EPI_NORM>), fg, fb, 0, s, g);
   else if (g.epi == EPI_SWIGLU) hipLaunchKernelGGL((k_gemm_finish<T, EPI_SWIGLU>), fg, fb, 0, s, g);
@@ -1486,9 +1559,11 @@ static bool gemm_rows_slices(const GemmLaunch &g, hipStream_t s) {
 }
 
 template <typename T, int RT, int NT, bool PAIR>
-static void split_launch(const GemmLaunch &g, hipStream_t s) {
+static void split_launch(const GemmLaunch &gl, hipStream_t s) {
+  GemmLaunch g = with_counts(gl, gl.split);
   const int groups = g.m.n_tiles / NT;
-  const dim3 grid((groups + 3) / 4, g.split);
+  g.nwg_x = (groups + 3) / 4;
+  const dim3 grid(g.nwg_x, g.split);
   bool staged = false;
   if constexpr (sizeof(T) == 2 && RT <= 2) {
     const int nk = g.m.nkb - g.kb_lo;
@@ -1510,6 +1585,13 @@ static bool gemm_slices(const GemmLaunch &g, hipStream_t s) {
     return false;
   }
   if (g.R > MAX_ROWS || g.split < 1) return false;   // the kernels below hold at most 4 row tiles
+  if constexpr (sizeof(T) == 2) {
+    // (a fusion FC that resolves its rows' tokens stays on the kernels below)
+    if (g.tile && !g.tok_out && g.x.pk && g.part && g.split <= g.m.nkb - g.kb_lo) {
+      tile_launch<Tile64, EPI_NORM>(g, s);
+      return true;
+    }
+  }
   if (g.nt == 8) {
     if (g.R <= 16) split_launch<T, 1, 8, PAIR>(g, s);
     else if (g.R <= 32) split_launch<T, 2, 8, PAIR>(g, s);
@@ -1592,7 +1674,9 @@ bool gemm_own_scales(const GemmLaunch &g, int n_parts) {
 bool lm_own_scales(int R, int n_parts) { return R <= MAX_ROWS && scales_fit(256, R, n_parts); }
 
 template <typename T, bool PAIR>
-static void lm_rt(const LmLaunch &g, hipStream_t s) {
+static void lm_rt(const LmLaunch &gl, hipStream_t s) {
+  LmLaunch g = gl;
+  g.norm.tsh = scale_tsh(256, g.R);
   const dim3 grid(g.n_wg), blk(256);
   if constexpr (sizeof(T) == 2) {
     if (g.gemv) {

@@ -81,6 +81,7 @@ struct RowNorm {
                                  // the consumer itself, or
   const float *scale = nullptr;  // row scales already reduced (launch_rowscale)
   int n_parts = 0;               // partial sums per row
+  int tsh = 0;                   // log2 of the threads that share a row (launcher)
   int n = 0;
   float eps = 0.f;
 };
@@ -91,6 +92,7 @@ struct KvArgs {
   const int32_t *ctx_lens;
   int mbps;        // block-table columns
   int bs;          // slots per block
+  int bs_sh;       // log2 bs, or -1 when it is not a power of two
   int n_blocks;    // pool blocks
   int n_seq;       // sequences described (valid values of a row's seq)
 };
@@ -131,9 +133,13 @@ struct GemmLaunch {
   Act x;
   int R;
   int kw;          // waves of the workgroup splitting K (1..16)
+  // set by the launcher, so that no kernel divides: k-blocks per part (wave
+  // or slice), quotient and remainder; log2 d; workgroups along x
+  int kq, kr, d_sh, nwg_x;
   int nt;          // tiles per workgroup (1 or 2)
   int gemv;        // 1: VALU GEMV main loop (bf16, R <= 4, staged fp32 activations)
   int split;       // > 0: batched path, K split over `split` workgroup slices
+  int tile;        // 1: K slices by the tile kernel at 64 rows
   int rowgrp;      // 1: more than MAX_ROWS rows: the tile kernel, split slices
   int tile0;       // first tile of m in the full QKV product (EPI_QKV of its q or its k, v rows)
   float *part;     // batched path: slice partial sums [split][R][N]

@@ -21,28 +21,12 @@ struct FcPrepArgs {
   uint32_t *err;
   int32_t *tok_out;   // optional [R]: the row's token, -1 if out of range
   int feat_only;      // the embedding half comes from a table: write the feature columns only
+  int R;
 };
 
+// 8 consecutive columns e0 .. e0 + 7 of row r
 template <typename T>
-__global__ __launch_bounds__(256) void k_fc_prep(FcPrepArgs a) {
-  __shared__ float shv[4];
-  __shared__ int shi[4];
-  const int r = blockIdx.y;
-  int tok;
-  if (a.lm.pval) {
-    tok = token_from_lm(a.lm, r, shv, shi);
-    if (a.lm.rec && blockIdx.x == 0 && threadIdx.x == 0) a.lm.rec[(size_t)r * a.lm.ld_rec] = tok;
-  } else {
-    tok = a.in.tokens[r];
-  }
-  const int e0 = (blockIdx.x * 256 + threadIdx.x) * 8;   // 8 consecutive columns
-  if (tok < 0 || tok >= a.V) {
-    // from the LM head, only a row of NaN logits leaves no token
-    if (e0 == 0) atomicOr(a.err, a.lm.pval && tok == NO_TOKEN ? ERRF_NONFINITE : ERRF_TOKEN);
-    tok = -1;
-  }
-  if (a.tok_out && e0 == 0) a.tok_out[r] = tok;
-  if (e0 >= a.H + a.F || (a.feat_only && e0 < a.H)) return;
+__device__ __forceinline__ void fc_prep_cols(const FcPrepArgs &a, int r, int tok, int e0) {
   const size_t o = a.X.at(r, e0);
   float v[8];
   bool exact;   // value already representable in the storage type
@@ -81,10 +65,61 @@ __global__ __launch_bounds__(256) void k_fc_prep(FcPrepArgs a) {
   }
 }
 
+// One row per workgroup column: the row's token from the previous LM head's
+// partials (a block reduction) or as given.
+template <typename T>
+__global__ __launch_bounds__(256) void k_fc_prep(FcPrepArgs a) {
+  __shared__ float shv[4];
+  __shared__ int shi[4];
+  const int r = blockIdx.y;
+  int tok;
+  if (a.lm.pval) {
+    tok = token_from_lm<256>(a.lm, r, shv, shi);
+    if (a.lm.rec && blockIdx.x == 0 && threadIdx.x == 0) a.lm.rec[(size_t)r * a.lm.ld_rec] = tok;
+  } else {
+    tok = a.in.tokens[r];
+  }
+  const int e0 = (blockIdx.x * 256 + threadIdx.x) * 8;
+  if (tok < 0 || tok >= a.V) {
+    // from the LM head, only a row of NaN logits leaves no token
+    if (e0 == 0) atomicOr(a.err, a.lm.pval && tok == NO_TOKEN ? ERRF_NONFINITE : ERRF_TOKEN);
+    tok = -1;
+  }
+  if (a.tok_out && e0 == 0) a.tok_out[r] = tok;
+  if (e0 >= a.H + a.F || (a.feat_only && e0 < a.H)) return;
+  fc_prep_cols<T>(a, r, tok, e0);
+}
+
+// Tiled planes, tokens as given: 4 rows x 512 columns per workgroup (adjacent
+// threads take adjacent rows, whose 16-byte pieces are adjacent in a fragment;
+// a row per workgroup wrote them 256 bytes apart).
+constexpr int PREP_ROWS = 4;
+template <typename T>
+__global__ __launch_bounds__(256) void k_fc_prep_rows(FcPrepArgs a) {
+  const int r = blockIdx.y * PREP_ROWS + (threadIdx.x & (PREP_ROWS - 1));
+  if (r >= a.R) return;
+  const int c = (blockIdx.x * (256 / PREP_ROWS) + threadIdx.x / PREP_ROWS) * 8;
+  const int e0 = c + (a.feat_only ? a.H : 0);
+  int tok = a.in.tokens[r];
+  const bool bad = tok < 0 || tok >= a.V;
+  if (bad) tok = -1;
+  if (c == 0) {
+    if (bad) atomicOr(a.err, ERRF_TOKEN);
+    if (a.tok_out) a.tok_out[r] = tok;
+  }
+  if (e0 < a.H + a.F) fc_prep_cols<T>(a, r, tok, e0);
+}
+
 void launch_fc_prep(bool bf16, int R, const RowsIn &in, const TokFromLm &lm, const void *embed,
                     int V, int H, int F, ActOut X, uint32_t *err, int32_t *tok_out, bool feat_only,
                     hipStream_t s) {
-  FcPrepArgs a{in, lm, embed, V, H, F, X, err, tok_out, feat_only ? 1 : 0};
+  FcPrepArgs a{in, lm, embed, V, H, F, X, err, tok_out, feat_only ? 1 : 0, R};
+  if (X.pk && !lm.pval) {   // bf16
+    const int cols = (feat_only ? 0 : H) + F, per = 8 * 256 / PREP_ROWS;
+    hipLaunchKernelGGL(k_fc_prep_rows<bf16_t>, dim3((cols + per - 1) / per, (R + PREP_ROWS - 1) / PREP_ROWS),
+                       dim3(256), 0, s, a);
+    return;
+  }
   dim3 grid((H + F + 2047) / 2048, R);
   if (bf16) hipLaunchKernelGGL(k_fc_prep<bf16_t>, grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL(k_fc_prep<float>, grid, dim3(256), 0, s, a);
@@ -99,7 +134,7 @@ __global__ __launch_bounds__(256) void k_rowscale(int R, const float *ss, int n_
   const int r = blockIdx.x;
   float acc = 0.f;
   for (int t = threadIdx.x; t < n_parts; t += blockDim.x) acc += ss[(size_t)t * R + r];
-  const float tot = block_sum(acc, sh);
+  const float tot = block_sum<4>(acc, sh);
   if (threadIdx.x == 0) scale[r] = 1.0f / sqrtf(tot / (float)n + eps);
 }
 
@@ -204,8 +239,8 @@ __global__ __launch_bounds__(256) void k_lm_combine(LmCombArgs a) {
       for (int j = 0; j < KB; ++j) { lv[j] = ov[j]; li[j] = oi[j]; }
     }
   }
-  const float M = block_max(m, shv);
-  const float S = block_sum(m == -INFINITY ? 0.f : s * expf(m - M), shv);
+  const float M = block_max<4>(m, shv);
+  const float S = block_sum<4>(m == -INFINITY ? 0.f : s * expf(m - M), shv);
   const float lse = M + logf(S);
   // each wave takes the best k of its lanes' lists (k rounds of a wave
   // arg-max over the list heads, on 64-bit candidate keys, no barriers),
@@ -297,7 +332,7 @@ __global__ __launch_bounds__(256) void k_lm_sample(LmSampleArgs a) {
 #pragma unroll
   for (int i = 0; i < SAMP_PER; ++i)
     if (mine(i)) m = fmaxf(m, vm[i]);
-  const float M = block_max(m, shv);
+  const float M = block_max<4>(m, shv);
   float w[SAMP_PER], loc = 0.f;
 #pragma unroll
   for (int i = 0; i < SAMP_PER; ++i) {
@@ -459,12 +494,12 @@ __global__ __launch_bounds__(256) void k_lm_topk(LmTopkArgs a) {
   float mx = -INFINITY;
 #pragma unroll
   for (int j = 0; j < TK_PER; ++j) mx = fmaxf(mx, v[j]);
-  const float M = block_max(mx, sh);
+  const float M = block_max<4>(mx, sh);
   float e = 0.f;
 #pragma unroll
   for (int j = 0; j < TK_PER; ++j)
     e += base + tid + 256 * j < a.V ? expf(v[j] * a.inv_temp - M * a.inv_temp) : 0.f;
-  const float S = block_sum(e, sh);
+  const float S = block_sum<4>(e, sh);
   const size_t pi = (size_t)r * a.n_wg + c;
   if (tid == 0) {
     a.pmax[pi] = M * a.inv_temp;
@@ -723,7 +758,7 @@ __global__ __launch_bounds__(256) void k_last_rows(LastRows a) {
     ((bf16_t *)a.x.lo)[i] = (bf16_t)f2bf(x - bf2f(h));
     ss += v * v;
   }
-  const float tot = block_sum(ss, sh);
+  const float tot = block_sum<4>(ss, sh);
   if (threadIdx.x == 0) a.scale[b] = 1.0f / sqrtf(tot / (float)a.H + a.eps);
 }
 

@@ -42,6 +42,7 @@ struct ProductPlan {
   int nt = 1;      // output tiles per wave
   int split = 0;   // > 0: K slices across workgroups (batched path, then a finish pass)
   int gemv = 0;    // 1: VALU GEMV main loop (bf16, at most GEMV_MAX_ROWS rows)
+  int tile = 0;    // 1: K slices by the tile kernel at 64 rows (33..64 rows, bf16)
   int rowgrp = 0;  // 1: tile kernel (more than MAX_ROWS rows, bf16), K slices, finish pass
 };
 
@@ -73,6 +74,19 @@ inline int rowgrp_rows(int n_tiles, int R, int split) {
   const long xg = (long)((n_tiles + ROWGRP_TILES - 1) / ROWGRP_TILES) * split;
   const long r128 = (xg * ((R + 127) / 128) + 255) / 256, r64 = (xg * ((R + 63) / 64) + 255) / 256;
   return r64 * 59 < r128 * 100 ? 64 : 128;
+}
+
+// K slices of a product over TILE64_MIN .. MAX_ROWS rows (bf16), which the
+// tile kernel takes at 64 rows per workgroup: about one workgroup per CU, at
+// least 4 k-blocks each, partials of at most 1/2 of the weight bytes.  (The
+// streaming kernels hold 4 row tiles there and one k-block at a time: 8B
+// layer over 41 rows, its products after the FC 138 -> 106 us.)
+constexpr int TILE64_MIN = 33;
+inline int tile64_split(int n_tiles, int nkb, int K, int R) {
+  int sp = 256 / ((n_tiles + ROWGRP_TILES - 1) / ROWGRP_TILES);
+  if (sp > nkb / 4) sp = nkb / 4;
+  if (sp > K / (4 * R)) sp = K / (4 * R);
+  return sp < 1 ? 1 : sp;
 }
 
 // K slices of a batched product at nt tiles per wave: at most one workgroup
@@ -149,6 +163,10 @@ inline ProductPlan plan_product(int n_tiles, int nkb, int K, int K_full, int R, 
       while (kw > 1 && ((kw - 1) * p.nt * rt > 48 || kw > nkb / 4)) --kw;
       p.kw = kw < 1 ? 1 : kw;
     }
+    if (bf16 && R >= TILE64_MIN) {
+      p.tile = 1;
+      p.split = tile64_split(n_tiles, nkb, K, R);
+    }
     return p;
   }
   // 1-2 rows: enough waves to cover HBM latency (about 16 per CU), at least
@@ -189,6 +207,10 @@ inline size_t product_partial_floats(int n_tiles, int nkb, int K, int rows_max) 
       for (int nt = 1; nt <= 8; nt *= 2) {
         if (n_tiles % nt) continue;
         const int s = batched_split(n_tiles, nt, nkb, K, rr);
+        if (s > sp) sp = s;
+      }
+      if (rr >= TILE64_MIN) {
+        const int s = tile64_split(n_tiles, nkb, K, rr);
         if (s > sp) sp = s;
       }
     }

@@ -557,6 +557,7 @@ static KvArgs kv_of(const prism_ctx *c, const prism_batch *b) {
   kv.ctx_lens = b->d_ctx_lens;
   kv.mbps = c->cfg.max_blocks_per_seq;
   kv.bs = c->cfg.kv_block_size;
+  kv.bs_sh = (kv.bs & (kv.bs - 1)) == 0 ? __builtin_ctz(kv.bs) : -1;
   kv.n_blocks = b->n_pool_blocks;
   kv.n_seq = b->batch;
   return kv;
@@ -614,6 +615,7 @@ static GemmLaunch gemm_of(const prism_ctx *c, const TiledMat &m, const Act &x, i
   g.nt = pl.nt;
   g.split = pl.split;
   g.gemv = pl.gemv;
+  g.tile = pl.tile;
   g.rowgrp = pl.rowgrp;
   if (R > GEMV_MAX_ROWS) g.part = c->part;
   return g;

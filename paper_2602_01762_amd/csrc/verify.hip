@@ -87,8 +87,8 @@ __global__ __launch_bounds__(256) void k_rows_soft(const float *__restrict__ x0,
       s += (expf(v[u].x - ref) + expf(v[u].y - ref)) + (expf(v[u].z - ref) + expf(v[u].w - ref));
     m = mn;
   }
-  const float M = block_max(m, sh);
-  const float S = block_sum(m == -INFINITY ? 0.f : s * expf(m - M), sh);
+  const float M = block_max<4>(m, sh);
+  const float S = block_sum<4>(m == -INFINITY ? 0.f : s * expf(m - M), sh);
   if (tid == 0) out[(size_t)row * parts + part] = SoftStat{M, S};
 }
 
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256) void k_rows_best(const float *__restrict__ x, 
     for (int i0 = lo + 4 * tid; i0 < hi && bi == NO_TOKEN; i0 += 4 * 256)
       for (int q = 3; q >= 0; --q)
         if (r[i0 + q] == -INFINITY) bi = i0 + q;
-  block_argmax(bv, bi, shv, shi);
+  block_argmax<4>(bv, bi, shv, shi);
   if (tid == 0) out[(size_t)row * parts + part] = BestStat{bv, bi};
 }
 
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(256) void k_verify_decide(VerifyChainArgs a) {
   const float *drow = w.mode == 1 ? a.dl + ((size_t)b * K + w.n) * V : trow;
   int lo, hi;
   slice_of(V, part, DRAW_SLICES, lo, hi);
-  const float sum = block_sum(slice_weight(a, w, w.mode, trow, drow, lo, hi), sh);
+  const float sum = block_sum<4>(slice_weight(a, w, w.mode, trow, drow, lo, hi), sh);
   if (tid == 0) {
     Draw *o = a.draw + b;
     o->sum[part] = sum;
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(256) void k_verify_draw(VerifyChainArgs a) {
     for (int p = 0; p < DRAW_SLICES; ++p) {
       int lo, hi;
       slice_of(V, p, DRAW_SLICES, lo, hi);
-      const float sum = block_sum(slice_weight(a, w, 0, trow, trow, lo, hi), sh);
+      const float sum = block_sum<4>(slice_weight(a, w, 0, trow, trow, lo, hi), sh);
       if (tid == 0) w.sum[p] = sum;
     }
     __syncthreads();

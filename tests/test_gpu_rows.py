@@ -96,3 +96,39 @@ def test_score_rows_share_their_trees_features(batch, nodes, hidden):
         assert np.max(np.abs(lg[b].cpu().numpy() - ref["logits"][b])) <= LOGIT_TOL["bf16"], b
     check_draft_kv(cfg, inp, ref["draft_kv"], seqs)
     dr.close()
+
+
+# 33 rows or more take the tile kernel at 64 rows per workgroup, 32 the
+# streaming kernels; 4 to 16 rows read the same fragments with lanes past the
+# last row folded onto row 0
+@pytest.mark.parametrize("batch", [2, 3, 16, 17, 32, 33, 47, 48, 64])
+@pytest.mark.parametrize("kv_block", [16, 24])
+def test_chain_row_counts(batch, kv_block):
+    """Chains at the edges of the row tiles, with a KV block size that is a
+    power of two and one that is not."""
+    cfg = SMALL_BF16_CHAIN.with_(name="small_rows_%d_%d" % (batch, kv_block), batch=batch, n_steps=2,
+                                 ctx_range=(1, 90), kv_block_size=kv_block)
+    dr, w, inp = gpu_setup(cfg)
+    out = dr.chain(inp, logits=True, hidden=True)
+    torch.cuda.synchronize()
+    assert dr.device_status() == 0
+    seqs = sorted({0, batch // 2, batch - 1})
+    orc, hi = oracle_for(cfg, w, inp, seqs)
+    log(cfg.name, check_chain(cfg, out, orc, hi, seqs, inp=inp))
+    dr.close()
+
+
+@pytest.mark.parametrize("head_dim,nq,nkv", [(32, 8, 2), (64, 4, 4), (128, 4, 1), (256, 2, 2)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_attention_head_dims(head_dim, nq, nkv, dtype):
+    """Every head width of the VALU and the matrix-core attention, contexts of
+    less than a step and of several chunks; positions up to 5000 rotate."""
+    cfg = SMALL_BF16_CHAIN.with_(name="small_d%d_%s" % (head_dim, dtype), head_dim=head_dim, n_q_heads=nq,
+                                 n_kv_heads=nkv, dtype=dtype, batch=2, n_steps=2, ctx_range=(5, 5000))
+    dr, w, inp = gpu_setup(cfg)
+    out = dr.chain(inp, logits=True, hidden=True)
+    torch.cuda.synchronize()
+    assert dr.device_status() == 0
+    orc, hi = oracle_for(cfg, w, inp, [0, 1])
+    log(cfg.name, check_chain(cfg, out, orc, hi, [0, 1], inp=inp))
+    dr.close()
