@@ -1320,7 +1320,10 @@ static bool gemm_epi(const GemmLaunch &gl, hipStream_t s) {
 //    current one; with two planes the lo fragments of the current k-block
 //    are read under the hi products, which saves their second register set.
 // Probes at 256 x 128, gate/up shape over 244 rows: 107 us; loads alone 77,
-// products alone 71, LDS reads alone 36.
+// products alone 71, LDS reads alone 36.  What the loads cost is their
+// number: 40 to 47 cycles of a CU per 1 KiB load to LDS at every shape, with
+// 3 to 7 k-blocks in flight alike and with the tiles' strides moved off
+// powers of two; the L2 serves 71-83% of them, LDS reads have no conflicts.
 template <int WM_, int WN_, int TM_, int TN_, bool PAIR_, int NBUF_>
 struct TileShape {
   static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, NBUF = NBUF_;
@@ -1332,10 +1335,12 @@ struct TileShape {
   static_assert(FR % NW == 0 && LDS <= 160 * 1024, "tile shape");
 };
 typedef TileShape<4, 2, 4, 4, true, 3> Tile128;    // 256 features x 128 rows, hi/lo planes
+typedef TileShape<2, 4, 8, 4, true, 3> Tile256;    // 256 features x 256 rows, hi/lo planes
 typedef TileShape<4, 2, 4, 2, true, 4> Tile64;     // 256 features x 64 rows, hi/lo planes
 typedef TileShape<4, 2, 4, 4, false, 4> Tile128X;  // 256 x 128, one plane, row-major
 typedef TileShape<2, 4, 8, 4, false, 4> Tile256X;  // 256 x 256, one plane, row-major
-static_assert(Tile128::FM == ROWGRP_TILES && Tile64::FM == ROWGRP_TILES, "row-group tiling");
+static_assert(Tile256::FM == ROWGRP_TILES && Tile128::FM == ROWGRP_TILES && Tile64::FM == ROWGRP_TILES,
+              "row-group tiling");
 
 // the wave's loads but the last N are in LDS and its LDS reads have
 // returned; then every wave of the workgroup
@@ -1438,8 +1443,25 @@ __device__ __forceinline__ void tile_loop(const TiledMat &m, int m0, const Act &
     read(q ^ 1, b1);
     dma(b);
     b = b1;
-    if constexpr (PAIR) mul(q, fl);
-    else mul(q, fh[q % QH]);
+    if constexpr (PAIR) {
+      mul(q, fl);
+      // LDS reads one per PR products, then the next stage's loads: bunched
+      // at the front they hold up the products issued behind them (8B LM
+      // head, 183 rows: 398 -> 389 us; one plane: no difference)
+      constexpr int M = TM * TN, D = TM + TN, PR = M - FW >= 2 * D ? 2 : 1, PV = M - PR * D >= 2 * FW ? 2 : 1;
+#pragma unroll
+      for (int i = 0; i < D; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, PR, 0);   // products
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);    // LDS reads
+      }
+#pragma unroll
+      for (int i = 0; i < FW; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);    // loads
+        __builtin_amdgcn_sched_group_barrier(0x008, PV, 0);
+      }
+    } else {
+      mul(q, fh[q % QH]);
+    }
     __builtin_amdgcn_sched_barrier(0);
   };
   int k = 0;
@@ -1544,9 +1566,11 @@ static bool gemm_rows_slices(const GemmLaunch &g, hipStream_t s) {
     else tile_launch<Tile128X, EPI_NORM>(g, s);
     return true;
   }
-  const bool small = rowgrp_rows(g.m.n_tiles, g.R, g.split) == 64;
+  const int rows = rowgrp_rows(g.m.n_tiles, g.R, g.split, g.epi == EPI_STORE);
+  const bool small = rows == 64;
   if (g.epi == EPI_STORE) {
-    if (small) tile_launch<Tile64, EPI_STORE>(g, s);
+    if (rows == 256) tile_launch<Tile256, EPI_STORE>(g, s);
+    else if (small) tile_launch<Tile64, EPI_STORE>(g, s);
     else tile_launch<Tile128, EPI_STORE>(g, s);
   } else if (direct) {
     if (small) tile_launch<Tile64, EPI_SWIGLU>(g, s);
@@ -1718,9 +1742,9 @@ void launch_lmhead(bool bf16, const LmLaunch &g, hipStream_t s) {
 // LM head over many rows at once, logits only (the target's tree-scoring
 // pass: up to LMR_MAX_ROWS rows in one launch): the tile kernel with one K
 // slice, its epilogue storing logits[r][v] = scale[r] * acc (the final
-// RMSNorm's row scale comes precomputed).  8B, 244 rows: 473 -> 419 us
-// (shortest of 20 calls) against workgroups of 64 rows that staged their
-// rows through registers.
+// RMSNorm's row scale comes precomputed).  8B, 244 rows: 449 us at 256 x 128,
+// 402 at 256 x 256 (medians of 12), which loads three fragments where two
+// workgroups of the former load four.
 void launch_lmhead_rows(const LmRowsArgs &a, hipStream_t s) {
   GemmLaunch g{};
   g.m = a.m;

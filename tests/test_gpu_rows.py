@@ -63,17 +63,21 @@ def test_long_catchup_flags_bad_tokens():
 
 # trees x (nodes + 1) rows: one tree below the small kernels' limit, whole
 # row tiles, one row past a tile, passes of whole trees; 1 node: 2 rows share
-# a feature row; hidden 480: no embedding table
-@pytest.mark.parametrize("batch,nodes,hidden", [(1, 60, 512), (2, 63, 512), (3, 42, 512), (1, 1, 512),
-                                                (64, 1, 512), (9, 28, 512), (3, 42, 480)])
-def test_score_rows_share_their_trees_features(batch, nodes, hidden):
+# a feature row; hidden 480: no embedding table; vocabulary 33040: more than
+# 128 groups of 256 ids, the last ragged, where a head over more than 192 rows
+# takes 256-row tiles
+@pytest.mark.parametrize("batch,nodes,hidden,vocab", [
+    (1, 60, 512, 5008), (2, 63, 512, 5008), (3, 42, 512, 5008), (1, 1, 512, 5008), (64, 1, 512, 5008),
+    (9, 28, 512, 5008), (3, 42, 480, 5008), (3, 63, 512, 33040), (4, 48, 512, 33040), (4, 63, 512, 33040),
+    (4, 60, 480, 33040)])
+def test_score_rows_share_their_trees_features(batch, nodes, hidden, vocab):
     """Scoring with target features that are not zero: every row of a tree
     fuses its sequence's feature row."""
     from oracle import Oracle
     from paper_2602_01762_amd import Drafter
     cfg = scoring_target(SMALL_BF16_CHAIN.with_(
         name="small_score_%dx%d" % (batch, nodes), batch=batch, tree_nodes=nodes, tree_width=1,
-        hidden=hidden, ctx_range=(3, 90)))
+        hidden=hidden, vocab=vocab, ctx_range=(3, 90)))
     w, inp = make_weights(cfg, "cuda"), make_inputs(cfg, "cuda")
     dr = Drafter(cfg)
     dr.load(w)
