@@ -758,8 +758,8 @@ template <typename T, int RT, int NT, bool PAIR, int EPI_K, int VR>
 __global__ __launch_bounds__((gemm_max_threads<RT, NT>())) void k_gemm(GemmLaunch g) {
   constexpr bool GX = EPI_K == EPI_NORM_GATHER;
   constexpr int EPI = GX ? EPI_NORM : EPI_K;
-  // dynamic LDS: [(kw - 1) * NT * RT * 64] f32x4 partial sums (kw with
-  // several tiles), kw floats,
+  // dynamic LDS (unsplit_lds_bytes): [(kw - 1) * NT * RT * 64] f32x4 partial
+  // sums (kw with several tiles), 64 kw floats,
   // then (GEMV path, VR > 0) VR * K floats of staged activations
   extern __shared__ f32x4 red[];
   __shared__ float rowscale[MAX_ROWS];
@@ -1284,10 +1284,7 @@ static bool gemm_epi(const GemmLaunch &gl, hipStream_t s) {
   GemmLaunch g = with_counts(gl, gl.kw);
   g.norm.tsh = scale_tsh(64 * g.kw, g.R);
   dim3 grid(g.m.n_tiles / NT);
-  const int parts = NT * RT > 1 && g.kw > 1 ? g.kw : g.kw - 1;     // partial sums kept per tile
-  size_t lds = (size_t)(parts * NT * RT * 64) * sizeof(f32x4) +
-               (size_t)64 * g.kw * sizeof(float);
-  if (VR > 0) lds += (size_t)VR * g.m.K * sizeof(float);
+  const size_t lds = unsplit_lds_bytes(g.kw, NT, RT, (size_t)VR * g.m.K * sizeof(float));
   if constexpr (VR > 0) {
     if (g.epi == EPI_NORM && g.gx.embed) {
       hipLaunchKernelGGL((k_gemm<T, RT, NT, PAIR, EPI_NORM_GATHER, VR>), grid, dim3(64 * g.kw), lds, s, g);

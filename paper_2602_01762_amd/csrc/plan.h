@@ -37,6 +37,19 @@ inline size_t gemv_lds_bytes(int R, int K) {
   return (size_t)vr * K * sizeof(float);
 }
 
+// LDS of an unsplit product's workgroup: the waves' partial sums, one KiB per
+// accumulator tile (several tiles: every wave leaves its own, as the waves
+// share the reduction; one tile: the first wave keeps its own), a row of 64
+// floats per wave, the row scales, and on the GEMV the staged rows.
+inline size_t unsplit_lds_bytes(int kw, int nt, int rt, size_t staged) {
+  const int sets = nt * rt > 1 && kw > 1 ? kw : kw - 1;
+  return (size_t)sets * nt * rt * 1024 + (size_t)64 * kw * sizeof(float) + staged;
+}
+constexpr size_t UNSPLIT_STATIC_LDS = MAX_ROWS * sizeof(float);   // the row scales (static)
+inline bool unsplit_lds_fits(int kw, int nt, int rt, size_t staged, size_t lds_limit) {
+  return unsplit_lds_bytes(kw, nt, rt, staged) + UNSPLIT_STATIC_LDS <= lds_limit;
+}
+
 struct ProductPlan {
   int kw = 1;      // waves of one workgroup splitting K
   int nt = 1;      // output tiles per wave
@@ -166,7 +179,9 @@ inline ProductPlan plan_product(int n_tiles, int nkb, int K, int K_full, int R, 
       const int groups = n_tiles / p.nt;
       int kw = 1024 / groups;
       if (kw > product_max_waves(rt, p.nt)) kw = product_max_waves(rt, p.nt);
-      while (kw > 1 && ((kw - 1) * p.nt * rt > 48 || kw > nkb / 4)) --kw;
+      while (kw > 1 && ((kw - 1) * p.nt * rt > 48 || kw > nkb / 4 ||
+                        !unsplit_lds_fits(kw, p.nt, rt, 0, lds_limit)))
+        --kw;
       p.kw = kw < 1 ? 1 : kw;
     }
     if (bf16 && R >= TILE64_MIN) {
@@ -185,13 +200,12 @@ inline ProductPlan plan_product(int n_tiles, int nkb, int K, int K_full, int R, 
   if (groups <= 512 && groups > 256 && kw > 8) kw = 8;
   if (kw > nkb / 4) kw = nkb / 4;
   if (kw < 1) kw = 1;
-  // LDS for the cross-wave sum: (kw - 1) * nt * rt KiB
-  while (kw > 1 && (kw - 1) * p.nt * rt > 48) --kw;
+  // LDS for the cross-wave sum (one tile per wave): kw - 1 KiB
+  while (kw > 1 && !unsplit_lds_fits(kw, p.nt, rt, 0, lds_limit)) --kw;
   p.kw = kw;
   // GEMV main loop (bf16) when the staged activations fit in the
   // workgroup's LDS next to the cross-wave partial sums
-  const size_t lds = gemv_lds_bytes(R, K_full) + (size_t)(kw - 1) * 64 * 16 + (size_t)64 * kw * 4;
-  p.gemv = bf16 && lds <= lds_limit ? 1 : 0;
+  p.gemv = bf16 && unsplit_lds_fits(kw, p.nt, rt, gemv_lds_bytes(R, K_full), lds_limit) ? 1 : 0;
   if (p.gemv) p.nt = 1;
   return p;
 }
@@ -225,12 +239,14 @@ inline size_t product_partial_floats(int n_tiles, int nkb, int K, int rows_max) 
   return most;
 }
 
-// Whether a plan's workgroup fits the instantiation it launches (the
-// launcher refuses a plan that does not).
-inline bool plan_fits(const ProductPlan &p, int R) {
+// Whether a plan's workgroup fits the instantiation it launches: its waves
+// (the launcher refuses a plan that does not) and its LDS.  K_full as in
+// plan_product.
+inline bool plan_fits(const ProductPlan &p, int R, int K_full, size_t lds_limit) {
   if (p.split > 0) return true;   // SPLIT_WAVES per workgroup
-  const int rt = p.gemv ? 1 : row_tiles(R);
-  return p.kw >= 1 && p.kw <= product_max_waves(rt, p.gemv ? 1 : p.nt);
+  const int rt = p.gemv ? 1 : row_tiles(R), nt = p.gemv ? 1 : p.nt;
+  return p.kw >= 1 && p.kw <= product_max_waves(rt, nt) &&
+         unsplit_lds_fits(p.kw, nt, rt, p.gemv ? gemv_lds_bytes(R, K_full) : 0, lds_limit);
 }
 
 // Rows per workgroup of the grouped tree attention (rows of one sequence

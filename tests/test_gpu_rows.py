@@ -122,6 +122,21 @@ def test_chain_row_counts(batch, kv_block):
     dr.close()
 
 
+def test_chain_shared_reduction_of_eight_tiles():
+    """Gate/up of 1600 tiles at 24 rows: 4 waves of 8 tiles x 2 row tiles,
+    66.8 KB of LDS (the plan is checked by test_shared_reduction_fits_the_lds)."""
+    cfg = SMALL_BF16_CHAIN.with_(name="small_ffn12800_h1024", batch=24, hidden=1024, ffn=12800, n_steps=2,
+                                 ctx_range=(1, 90))
+    dr, w, inp = gpu_setup(cfg)
+    out = dr.chain(inp, logits=True, hidden=True)
+    torch.cuda.synchronize()
+    assert dr.device_status() == 0
+    seqs = [0, 11, 23]
+    orc, hi = oracle_for(cfg, w, inp, seqs)
+    log(cfg.name, check_chain(cfg, out, orc, hi, seqs, inp=inp))
+    dr.close()
+
+
 @pytest.mark.parametrize("head_dim,nq,nkv", [(32, 8, 2), (64, 4, 4), (128, 4, 1), (256, 2, 2)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_attention_head_dims(head_dim, nq, nkv, dtype):

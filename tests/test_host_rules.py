@@ -67,7 +67,7 @@ int main() {
       std::scanf("%d %d %d %d %d %d %d %ld", &nt, &nkb, &K, &Kf, &R, &qkv, &bf, &lds);
       ProductPlan p = plan_product(nt, nkb, K, Kf, R, qkv != 0, bf != 0, (size_t)lds);
       const int rt = p.gemv ? 1 : row_tiles(R);
-      std::printf("%d %d %d %d %d %d %d\n", p.kw, p.nt, p.split, p.gemv, plan_fits(p, R) ? 1 : 0,
+      std::printf("%d %d %d %d %d %d %d\n", p.kw, p.nt, p.split, p.gemv, plan_fits(p, R, Kf, (size_t)lds) ? 1 : 0,
                   product_max_waves(rt, p.gemv ? 1 : p.nt), p.rowgrp);
     } else if (!std::strcmp(cmd, "grp")) {    // bf16 nq nkv d w
       int bf, nq, nkv, d, w;
@@ -290,6 +290,18 @@ def test_gate_up_tiles_fill_whole_rounds(driver):
         kw, nt, split, gemv, fits, maxw, rowgrp = (int(x) for x in o.split())
         assert (nt, split, gemv, fits, rowgrp) == (7, 0, 0, 1, 0), o
         assert n_tiles // nt == groups
+
+
+@pytest.mark.parametrize("n_tiles,K", [(1664, 1024), (1600, 1024), (1728, 5120), (2048, 4096)])
+def test_shared_reduction_fits_the_lds(driver, n_tiles, K):
+    """Gate/up of FFN 13312, 12800, 13824 and 16384 at 17-32 rows: 8 tiles x 2
+    row tiles per wave, whose 4 waves each leave 16 KiB of partial sums.  A
+    64 KiB workgroup does not hold them beside its row scales."""
+    for R, (lds, waves) in itertools.product((17, 24, 32), ((163840, 4), (65536, 3))):
+        o = driver("plan %d %d %d %d %d 0 1 %d\n" % (n_tiles, K // 32, K, K, R, lds))[0]
+        kw, nt, split, gemv, fits, maxw, rowgrp = (int(x) for x in o.split())
+        assert (kw, nt, split, fits) == (waves, 8, 0, 1), (R, lds, o)
+        assert kw * nt * 2 * 1024 + 64 * kw * 4 + 64 * 4 <= lds
 
 
 def test_row_group_plans_for_scoring_passes(driver):
