@@ -1518,9 +1518,6 @@ void k_gemm_tile(GemmLaunch g) {
 template <typename S, int EPI>
 static void tile_launch(const GemmLaunch &gl, hipStream_t s) {
   GemmLaunch g = with_counts(gl, gl.split);
-  // more than 64 KiB of dynamic LDS has to be allowed, on each device
-  (void)hipFuncSetAttribute((const void *)k_gemm_tile<S, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)S::LDS);
   const long wgs = (long)((g.m.n_tiles + S::FM - 1) / S::FM) * ((g.R + 16 * S::FN - 1) / (16 * S::FN)) * g.split;
   g.nwg_x = (int)((wgs + 7) / 8 * 8);
   hipLaunchKernelGGL((k_gemm_tile<S, EPI>), dim3(g.nwg_x), dim3(64 * S::NW), S::LDS, s, g);
