@@ -1739,7 +1739,7 @@ void launch_lmhead(bool bf16, const LmLaunch &g, hipStream_t s) {
 // RMSNorm's row scale comes precomputed).  8B, 244 rows: 449 us at 256 x 128,
 // 402 at 256 x 256 (medians of 12), which loads three fragments where two
 // workgroups of the former load four.
-void launch_lmhead_rows(const LmRowsArgs &a, hipStream_t s) {
+bool launch_lmhead_rows(const LmRowsArgs &a, hipStream_t s) {
   GemmLaunch g{};
   g.m = a.m;
   g.x = a.x;
@@ -1750,14 +1750,14 @@ void launch_lmhead_rows(const LmRowsArgs &a, hipStream_t s) {
   g.y = a.logits;
   g.ldy = a.ld_logits;
   g.norm.scale = a.scale;
-  gemm_rows_slices(g, s);
+  return gemm_rows_slices(g, s);
 }
 
 // Embedding half of a fusion FC for every token: T[v][n] = sum_{k < H}
 // W[n][k] E[v][k], the tile kernel over E's rows in place (one exact plane),
 // fp32 accumulation in k order.  Runs at load time; 8B: 4.3 TFLOP per set in
 // 29.7 -> 3.8 ms (1.1 PFLOP/s; one 16-row load per product before).
-void launch_embed_table(const TiledMat &w, const void *embed, int V, int H, float *T, hipStream_t s) {
+bool launch_embed_table(const TiledMat &w, const void *embed, int V, int H, float *T, hipStream_t s) {
   GemmLaunch g{};
   g.m = w;
   g.x.hi = embed;
@@ -1769,7 +1769,7 @@ void launch_embed_table(const TiledMat &w, const void *embed, int V, int H, floa
   g.y = T;
   g.ldy = w.N;
   g.kb_n = H / 32;
-  gemm_rows_slices(g, s);
+  return gemm_rows_slices(g, s);
 }
 
 // Repack a row-major [n_src_rows, K] matrix into the tiled layout: source row

@@ -199,7 +199,7 @@ struct LmLaunch {
 // ---- launchers (gemm.hip) -------------------------------------------------
 // false (nothing launched): the plan's workgroup exceeds the bound of the
 // kernel instantiation it selects
-bool launch_gemm(bool bf16, const GemmLaunch &g, hipStream_t s);
+[[nodiscard]] bool launch_gemm(bool bf16, const GemmLaunch &g, hipStream_t s);
 void launch_lmhead(bool bf16, const LmLaunch &g, hipStream_t s);
 // LM head over up to LMR_MAX_ROWS rows in one launch, logits only (bf16,
 // the tile kernel): logits[r][v] = scale[r] * (W x_r)[v]
@@ -211,12 +211,13 @@ struct LmRowsArgs {
   const float *scale;     // [R] row scales, or NULL
   float *logits; long ld_logits;
 };
-void launch_lmhead_rows(const LmRowsArgs &g, hipStream_t s);
+// false (nothing launched): a product that the kernel does not take
+[[nodiscard]] bool launch_lmhead_rows(const LmRowsArgs &g, hipStream_t s);
 // finish pass alone over g.R rows, of slice partials that an earlier product
 // left in g.part (EPI_NORM)
 void launch_gemm_finish(const GemmLaunch &g, hipStream_t s);
 // the product alone (K slices to g.part), without its finish pass
-bool launch_gemm_slices(const GemmLaunch &g, hipStream_t s);
+[[nodiscard]] bool launch_gemm_slices(const GemmLaunch &g, hipStream_t s);
 int lm_workgroups(int n_tiles, int nt);
 // partial sums of squares per row that an EPI_NORM launch writes
 int gemm_ss_parts(const GemmLaunch &g);
@@ -277,8 +278,9 @@ void launch_verify_tree(int B, int nodes, int V, const float *tl, const int32_t 
                         void *stats, hipStream_t s);
 // T[v][n] = sum_{k < H} W[n][k] E[v][k] for every token v: the embedding
 // half of a fusion FC in the tiled layout (k-blocks [0, H / 32) of each tile)
-// times the embedding rows, fp32 [V, N]
-void launch_embed_table(const TiledMat &w, const void *embed, int V, int H, float *T, hipStream_t s);
+// times the embedding rows, fp32 [V, N]; false: nothing launched
+[[nodiscard]] bool launch_embed_table(const TiledMat &w, const void *embed, int V, int H, float *T,
+                                      hipStream_t s);
 // top-k partials from stored logits [R, ld] (rows whose LM head skips its
 // epilogue): n_wg = lm_topk_chunks(V) chunks per row, topk <= TK_MAXK, in the
 // layout of the LM-head partials

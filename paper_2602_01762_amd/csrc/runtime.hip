@@ -451,7 +451,9 @@ prism_status prism_draft_load_shared(prism_ctx *c, const void *d_embed, const vo
   HIPCHK(c, hipMemcpyAsync(c->gf, d_final_norm, (size_t)c->H * c->esz, hipMemcpyDeviceToDevice, s));
   for (auto &S : c->sets) {   // embedding tables of the sets already loaded
     if (!S.tab || !S.loaded) continue;
-    launch_embed_table(S.fc, c->embed, c->V, c->H, S.tab, s);
+    S.tab_ready = false;
+    if (!launch_embed_table(S.fc, c->embed, c->V, c->H, S.tab, s))
+      return fail(c, PRISM_ERR_SHAPE, "embedding table [%d, %d] out of its kernel's range", c->V, c->H);
     HIPCHK(c, hipGetLastError());
     S.tab_ready = true;
   }
@@ -946,7 +948,7 @@ static prism_status run_graph(prism_ctx *c, const std::vector<uintptr_t> &key, h
     c->prof_used = 0;
     enqueue(s);
     c->prof_last = c->prof_used;
-    if (c->enq_bad) return fail(c, PRISM_ERR_SHAPE, "a product plan exceeds its kernel's workgroup bound");
+    if (c->enq_bad) return fail(c, PRISM_ERR_SHAPE, "a product is out of its kernel's range");
     HIPCHK(c, hipGetLastError());
     return PRISM_OK;
   }
@@ -962,7 +964,7 @@ static prism_status run_graph(prism_ctx *c, const std::vector<uintptr_t> &key, h
     if (ee == hipSuccess && (le != hipSuccess || c->enq_bad)) (void)hipGraphDestroy(graph);
     if (le != hipSuccess) return fail(c, PRISM_ERR_HIP, "launch during capture: %s", hipGetErrorString(le));
     if (ee != hipSuccess) return fail(c, PRISM_ERR_HIP, "hipStreamEndCapture: %s", hipGetErrorString(ee));
-    if (c->enq_bad) return fail(c, PRISM_ERR_SHAPE, "a product plan exceeds its kernel's workgroup bound");
+    if (c->enq_bad) return fail(c, PRISM_ERR_SHAPE, "a product is out of its kernel's range");
     hipGraphExec_t exec;
     hipError_t ie = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
@@ -1029,7 +1031,7 @@ prism_status prism_draft_step(prism_ctx *c, int32_t k, const prism_step_io *io, 
   c->prof_used = 0;
   enqueue_pass(c, p, kv_of(c, b), s);
   c->prof_last = c->prof_used;
-  if (c->enq_bad) return fail(c, PRISM_ERR_SHAPE, "a product plan exceeds its kernel's workgroup bound");
+  if (c->enq_bad) return fail(c, PRISM_ERR_SHAPE, "a product is out of its kernel's range");
   HIPCHK(c, hipGetLastError());
   return PRISM_OK;
 }
@@ -1426,7 +1428,7 @@ prism_status prism_score_tree(prism_ctx *c, const prism_batch *batch, int32_t n_
         a.scale = c->lmr_scale;
         a.logits = d_logits + (size_t)r0 * V;
         a.ld_logits = V;
-        launch_lmhead_rows(a, s);
+        if (!launch_lmhead_rows(a, s)) c->enq_bad = true;
       }
     }
   });

@@ -405,3 +405,44 @@ def test_plans_on_random_shapes(driver):
         if split > 0:
             assert split <= nkb, (bf, nt, nkb, R, split)
             assert split * R * 16 * nt <= size, (bf, nt, nkb, R, split, size)
+
+
+REFUSED = r"""
+#include <cstdio>
+#include "internal.h"
+using namespace prism;
+int main() {
+  static char w[16];   // never read: the calls below launch nothing
+  TiledMat m;
+  m.w = w; m.N = 64; m.K = 64; m.n_tiles = 4; m.nkb = 2;
+  LmRowsArgs rows{};   // no output rows, no operand planes
+  rows.m = m;
+  rows.R = 0;
+  const bool a = launch_lmhead_rows(rows, nullptr);
+  const bool b = launch_embed_table(m, w, 0, 64, (float *)w, nullptr);
+  GemmLaunch g{};
+  g.m = m; g.R = 65; g.rowgrp = 1; g.split = 3;   // more slices than k-blocks
+  g.x.hi = g.x.lo = w; g.x.pk = 1; g.x.ld = 64; g.part = (float *)w;
+  const bool c = launch_gemm(true, g, nullptr);
+  g.rowgrp = 0; g.split = 1;                      // 65 rows without the tile kernel
+  const bool d = launch_gemm_slices(g, nullptr);
+  std::printf("%d%d%d%d\n", a, b, c, d);
+}
+"""
+
+
+def test_refused_launches_are_reported(tmp_path):
+    """A product that its kernel does not take launches nothing, and every
+    launcher returns that to the runtime, which fails the call with
+    PRISM_ERR_SHAPE: also the LM head over many rows and the embedding table."""
+    from paper_2602_01762_amd import binding
+    if not os.path.exists(binding.LIB_PATH):
+        pytest.skip("library not built")
+    src, exe = tmp_path / "refused.cpp", tmp_path / "refused"
+    src.write_text(REFUSED)
+    libdir = os.path.dirname(binding.LIB_PATH)
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", CSRC, str(src),
+                    "-o", str(exe), "-L", libdir, "-l:libprism_draft.so", "-Wl,-rpath," + libdir,
+                    "-Wl,-rpath,/opt/rocm/lib", "-Wl,--allow-shlib-undefined"], check=True)
+    out = subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout
+    assert out.strip() == "0000"
