@@ -1705,10 +1705,9 @@ static void lm_rt(const LmLaunch &gl, hipStream_t s) {
       return;
     }
   }
-  if (g.nt == 8) {   // eight tiles per wave share each B fragment
+  if (g.nt == 8) {   // eight tiles per wave share each B fragment (up to 32 rows: lm_head_tiles)
     if (g.R <= 16) hipLaunchKernelGGL((k_lmhead<T, 1, 8, PAIR, 0>), grid, blk, 0, s, g);
-    else if (g.R <= 32) hipLaunchKernelGGL((k_lmhead<T, 2, 8, PAIR, 0>), grid, blk, 0, s, g);
-    else hipLaunchKernelGGL((k_lmhead<T, 4, 8, PAIR, 0>), grid, blk, 0, s, g);
+    else hipLaunchKernelGGL((k_lmhead<T, 2, 8, PAIR, 0>), grid, blk, 0, s, g);
     return;
   }
   if (g.nt == 4) {   // four tiles per wave share each B fragment (batched rows)

@@ -59,6 +59,23 @@ struct ProductPlan {
   int rowgrp = 0;  // 1: tile kernel (more than MAX_ROWS rows, bf16), K slices, finish pass
 };
 
+// Vocab tiles per wave of the LM head.  GEMV (one row): four consecutive
+// tiles when that still gives about four waves per CU (longer weight streams,
+// one round of workgroups).  Batched rows: several tiles share the B
+// fragments a wave loads; 8 up to 32 rows (at 16 rows 176 -> 166 us against 4
+// tiles, the B stream being half as large per weight byte).  Above, with 4
+// row tiles, 4: at 8 a CU holds one workgroup (131 KB of LDS), whose waves
+// load a k-block, wait and multiply in turn; at 4 it holds two, and a narrow
+// vocabulary spreads over twice the CUs (8B LM head at 33 / 48 / 64 rows 255 /
+// 258 / 273 -> 217 / 223 / 251 us; 32000 ids, H 2048, 40 rows: the 5-step
+// chain 1079 -> 838 us.  While the rows were row-major, 8 was the faster).
+inline int lm_head_tiles(int n_tiles, int R, bool gemv) {
+  if (gemv) return n_tiles % 16 == 0 && n_tiles / 4 >= 1024 ? 4 : 1;
+  if (R <= LM_GEMV_MAX_ROWS) return 1;
+  if (R <= 32 && n_tiles % 8 == 0) return 8;
+  return n_tiles % 4 == 0 ? 4 : n_tiles % 2 == 0 ? 2 : 1;
+}
+
 // Products over more than MAX_ROWS rows (bf16: tree-scoring passes of whole
 // trees up to 256 rows, the front of a long catch-up): the tile kernel.  A
 // workgroup of 8 waves takes ROWGRP_TILES output tiles (256 features)

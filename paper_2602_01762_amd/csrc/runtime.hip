@@ -839,19 +839,7 @@ static void enqueue_back(prism_ctx *c, const Pass &p, const KvArgs &kv, const fl
   lmg.topk = p.topk;
   lmg.inv_temp = p.u ? p.inv_temp : 1.f;
   lmg.gemv = lm_is_gemv(c, R) ? 1 : 0;
-  lmg.nt = 1;
-  // one row: four consecutive vocab tiles per wave when that still gives
-  // about four waves per CU (longer weight streams, one round of workgroups)
-  if (lmg.gemv && c->lm.n_tiles % 16 == 0 && c->lm.nkb % 16 == 0 && c->lm.n_tiles / 4 >= 1024)
-    lmg.nt = 4;
-  // batched rows: several vocab tiles per wave share B fragments; 8 up to
-  // 32 rows (at 16 rows: 176 -> 166 us against 4 tiles, the B stream being
-  // half as large per weight byte), 4 above
-  if (!lmg.gemv && R > LM_GEMV_MAX_ROWS) {
-    if (c->lm.n_tiles % 8 == 0) lmg.nt = 8;
-    else if (c->lm.n_tiles % 4 == 0) lmg.nt = 4;
-    else if (c->lm.n_tiles % 2 == 0) lmg.nt = 2;
-  }
+  lmg.nt = lm_head_tiles(c->lm.n_tiles, R, lmg.gemv != 0);
   lmg.n_wg = lm_workgroups(c->lm.n_tiles, lmg.nt);
   lmg.norm = norm_for(c, c->ss_h, parts_h, lm_own_scales(R, parts_h), c->sc_h, R, s);
   lmg.logits = p.logits;

@@ -122,6 +122,21 @@ def test_chain_row_counts(batch, kv_block):
     dr.close()
 
 
+# 320 vocab tiles: 8 per wave up to 32 rows, 4 above; 322: 2 per wave
+@pytest.mark.parametrize("batch,vocab", [(32, 5120), (33, 5120), (48, 5120), (64, 5120), (49, 5152)])
+def test_chain_lm_head_tiles(batch, vocab):
+    cfg = SMALL_BF16_CHAIN.with_(name="small_lm_%d_%d" % (batch, vocab), batch=batch, vocab=vocab, n_steps=2,
+                                 ctx_range=(1, 90))
+    dr, w, inp = gpu_setup(cfg)
+    out = dr.chain(inp, logits=True, hidden=True)
+    torch.cuda.synchronize()
+    assert dr.device_status() == 0
+    seqs = sorted({0, batch // 2, batch - 1})
+    orc, hi = oracle_for(cfg, w, inp, seqs)
+    log(cfg.name, check_chain(cfg, out, orc, hi, seqs, inp=inp))
+    dr.close()
+
+
 def test_chain_shared_reduction_of_eight_tiles():
     """Gate/up of 1600 tiles at 24 rows: 4 waves of 8 tiles x 2 row tiles,
     66.8 KB of LDS (the plan is checked by test_shared_reduction_fits_the_lds)."""

@@ -87,6 +87,10 @@ int main() {
       int nt, nkb, K, rm;
       std::scanf("%d %d %d %d", &nt, &nkb, &K, &rm);
       std::printf("%zu\n", product_partial_floats(nt, nkb, K, rm));
+    } else if (!std::strcmp(cmd, "lmt")) {    // n_tiles R gemv
+      int nt, R, gv;
+      std::scanf("%d %d %d", &nt, &R, &gv);
+      std::printf("%d\n", lm_head_tiles(nt, R, gv != 0));
     } else if (!std::strcmp(cmd, "sgrp")) {   // bf16 nq nkv d
       int bf, nq, nkv, d;
       std::scanf("%d %d %d %d", &bf, &nq, &nkv, &d);
@@ -405,6 +409,25 @@ def test_plans_on_random_shapes(driver):
         if split > 0:
             assert split <= nkb, (bf, nt, nkb, R, split)
             assert split * R * 16 * nt <= size, (bf, nt, nkb, R, split, size)
+
+
+def test_lm_head_tiles(driver):
+    """Vocab tiles per wave: a divisor of the tile count; 8 up to 32 rows only,
+    4 above, where 8 leave one workgroup per CU; the benchmark's workgroup
+    count of one launch follows the same rule."""
+    import bench
+    for cfg, R in itertools.product(list(CONFIGS.values()) + [SMALL_BF16_CHAIN, SMALL_F32_CHAIN,
+                                                              SMALL_BF16_CHAIN.with_(vocab=5120)],
+                                    (1, 2, 16, 17, 32, 33, 48, 64)):
+        n, nkb = cfg.vocab // 16, cfg.hidden // 32
+        gemv = R == 1 and cfg.dtype == "bf16" and nkb % 16 == 0
+        nt = int(driver("lmt %d %d %d\n" % (n, R, gemv))[0])
+        assert nt in (1, 2, 4, 8) and n % nt == 0
+        if not gemv:
+            want = 1 if R == 1 else next(k for k in ((8, 4, 2, 1) if R <= 32 else (4, 2, 1)) if n % k == 0)
+            assert nt == want, (cfg.name, R)
+        if R > 1 or gemv:
+            assert bench.lm_workgroups(cfg, R) == -(-(n // nt) // 4), (cfg.name, R)
 
 
 REFUSED = r"""
