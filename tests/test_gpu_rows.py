@@ -137,6 +137,23 @@ def test_chain_lm_head_tiles(batch, vocab):
     dr.close()
 
 
+@pytest.mark.parametrize("batch", [33, 40, 64])
+def test_chain_steps_without_prep_above_32_rows(batch):
+    """Steps >= 2 whose fusion FC has at least a workgroup per row (hidden 2048:
+    8 tile groups x 8 to 15 slices) resolve their tokens in that product, on
+    the streaming kernel with the slices of the tile kernel's plan."""
+    cfg = SMALL_BF16_CHAIN.with_(name="small_direct_%d" % batch, batch=batch, hidden=2048, n_steps=3,
+                                 ctx_range=(1, 60))
+    dr, w, inp = gpu_setup(cfg)
+    out = dr.chain(inp, logits=True, hidden=True)
+    torch.cuda.synchronize()
+    assert dr.device_status() == 0
+    seqs = sorted({0, batch // 2, batch - 1})
+    orc, hi = oracle_for(cfg, w, inp, seqs)
+    log(cfg.name, check_chain(cfg, out, orc, hi, seqs, inp=inp))
+    dr.close()
+
+
 def test_chain_shared_reduction_of_eight_tiles():
     """Gate/up of 1600 tiles at 24 rows: 4 waves of 8 tiles x 2 row tiles,
     66.8 KB of LDS (the plan is checked by test_shared_reduction_fits_the_lds)."""
