@@ -1321,9 +1321,19 @@ static bool gemm_epi(const GemmLaunch &gl, hipStream_t s) {
 // number: 40 to 47 cycles of a CU per 1 KiB load to LDS at every shape, with
 // 3 to 7 k-blocks in flight alike and with the tiles' strides moved off
 // powers of two; the L2 serves 71-83% of them, LDS reads have no conflicts.
-template <int WM_, int WN_, int TM_, int TN_, bool PAIR_, int NBUF_>
+//
+// FOLD: a running fp32 sum takes at most FOLD k-blocks, then it is added to a
+// second one (FOLD even; 0: one sum over the slice, where the registers hold
+// no second one: the LM head and the embedding tables).  These shapes take
+// fewer and longer slices than the kernels before them, and one sum over a
+// slice left the outputs further from their 64-bit values: cache values of
+// 1531 accepted rows (8B) on the other side of a bf16 rounding 3931 before,
+// 4036 without and 3900 with; logits over the same cache at 33 rows 4.115e-6,
+// 4.127e-6 and 4.107e-6 of their norm.  Cost: none at 64 rows, 0.5% of the
+// front's FC.
+template <int WM_, int WN_, int TM_, int TN_, bool PAIR_, int NBUF_, int FOLD_ = 0>
 struct TileShape {
-  static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, NBUF = NBUF_;
+  static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, NBUF = NBUF_, FOLD = FOLD_;
   static constexpr bool PAIR = PAIR_;
   static constexpr int NW = WM * WN, FM = WM * TM, FN = WN * TN;
   static constexpr int FR = FM + (PAIR ? 2 : 1) * FN;   // fragments per stage
@@ -1331,10 +1341,10 @@ struct TileShape {
   static constexpr size_t LDS = (size_t)NBUF * FR * 1024;
   static_assert(FR % NW == 0 && LDS <= 160 * 1024, "tile shape");
 };
-typedef TileShape<4, 2, 4, 4, true, 3> Tile128;    // 256 features x 128 rows, hi/lo planes
+typedef TileShape<4, 2, 4, 4, true, 3, 32> Tile128;    // 256 features x 128 rows, hi/lo planes
 typedef TileShape<2, 4, 8, 4, true, 3> Tile256;    // 256 features x 256 rows, hi/lo planes
-typedef TileShape<4, 2, 4, 2, true, 4> Tile64;     // 256 features x 64 rows, hi/lo planes
-typedef TileShape<4, 2, 4, 4, false, 4> Tile128X;  // 256 x 128, one plane, row-major
+typedef TileShape<4, 2, 4, 2, true, 4, 16> Tile64;     // 256 features x 64 rows, hi/lo planes
+typedef TileShape<4, 2, 4, 4, false, 4, 32> Tile128X;  // 256 x 128, one plane, row-major
 typedef TileShape<2, 4, 8, 4, false, 4> Tile256X;  // 256 x 256, one plane, row-major
 static_assert(Tile256::FM == ROWGRP_TILES && Tile128::FM == ROWGRP_TILES && Tile64::FM == ROWGRP_TILES,
               "row-group tiling");
@@ -1462,11 +1472,39 @@ __device__ __forceinline__ void tile_loop(const TiledMat &m, int m0, const Act &
     __builtin_amdgcn_sched_barrier(0);
   };
   int k = 0;
-  for (; k + 1 < n; k += 2) {
-    step(0);
-    step(1);
+  auto run = [&](int end) {   // whole pairs of k-blocks
+#pragma unroll 1
+    for (; k + 1 < end; k += 2) {
+      step(0);
+      step(1);
+    }
+  };
+  if constexpr (S::FOLD > 0) {
+    f32x4 sum[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    while (k + S::FOLD < n) {
+      run(k + S::FOLD);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          sum[i][j] += acc[i][j];
+          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    run(n);
+    if (k < n) step(0);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] += sum[i][j];
+  } else {
+    run(n);
+    if (k < n) step(0);
   }
-  if (k < n) step(0);
   // loads still in flight write this workgroup's LDS: it must not end before
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }

@@ -61,6 +61,40 @@ def test_long_catchup_flags_bad_tokens():
     dr.close()
 
 
+def test_long_front_sums_stay_short():
+    """2048 accepted rows at hidden 2304: one K slice of 384 k-blocks of the
+    fusion FC.  All terms positive, so the running sum grows steadily and each
+    addition rounds at about the sum's size so far: 2^-24 / sqrt(3) / 1.44 of
+    it (rms).  One chain of 384 additions is off by sqrt(384 / 3) = 11.3 of
+    these (2.7e-7); sums of at most 32, then 12 of those, by sqrt(32 / 3 / 12)
+    and sqrt(12 / 3) = 2.2 (5e-8, and a few more roundings after the sum).  The
+    line lies at 5.5.  With W_o, W_down and E zero the step's hidden row is the
+    FC's output."""
+    H, F, T = 2304, 12288, 2048
+    cfg = SMALL_BF16_CHAIN.with_(name="small_long_sum", hidden=H, feat_width=F, batch=1, n_new=(T, T), n_steps=1,
+                                 n_sets=1, f_map=(0,), ctx_range=(0, 0))
+    w, inp = make_weights(cfg, "cuda"), make_inputs(cfg, "cuda")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    ps = w.sets[0]
+    ps.w_fc.copy_(torch.rand(ps.w_fc.shape, generator=g, device="cuda") + 0.5)
+    inp.new_features.copy_(torch.rand(inp.new_features.shape, generator=g, device="cuda") + 0.5)
+    for t in (ps.w_o, ps.w_down, w.embed):
+        t.zero_()
+    from paper_2602_01762_amd import Drafter
+    dr = Drafter(cfg)
+    dr.load(w)
+    out = dr.chain_catchup(inp, hidden=True)
+    torch.cuda.synchronize()
+    assert dr.device_status() == 0
+    want = ps.w_fc[:, H:].double().cpu().numpy() @ inp.new_features[-1].double().cpu().numpy()
+    rel = out["hidden"][0, 0].double().cpu().numpy() / want - 1
+    rms = float(np.sqrt(np.mean(rel ** 2)))
+    log(cfg.name, rms)
+    assert rms <= 5.5 * 2 ** -24 / 3 ** 0.5 / 1.44
+    dr.close()
+
+
 # trees x (nodes + 1) rows: one tree below the small kernels' limit, whole
 # row tiles, one row past a tile, passes of whole trees; 1 node: 2 rows share
 # a feature row; hidden 480: no embedding table; vocabulary 33040: more than
