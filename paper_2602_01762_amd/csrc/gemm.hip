@@ -23,6 +23,7 @@
 // RMSNorm (reduced by the consumer itself), the SwiGLU product, or q and the
 // rotated k, v cache slots.
 #include "device.h"
+#include "rotation.h"
 
 namespace prism {
 
@@ -549,40 +550,14 @@ static GemmLaunch with_counts(GemmLaunch g, int parts) {
   return g;
 }
 
-// Rotation of a lane's 4 dims at a position, in fp64: the angle less its
-// nearest multiple of pi/2, the Taylor sums of sine and cosine on what is
-// left (|r| <= pi/4: the terms dropped are below 1e-11), and the quadrant.
-// No branch and no scratch (the library's sincosf keeps a large-argument
-// path), but still a few hundred cycles of one wave, so the kernels compute
-// it while their first loads are in flight.
+// Rotation of a lane's 4 dims at a position.
 struct Rot {
   float c[4], s[4];
 };
 __device__ __forceinline__ Rot rotation(int pos, const double (&freq)[4]) {
   Rot t;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const double ang = (double)pos * freq[i];
-    const double q = rint(ang * 0.63661977236758134);           // 2 / pi
-    double r = fma(-q, 1.5707963267948966, ang);                 // pi / 2, high and low words
-    r = fma(-q, 6.123233995736766e-17, r);
-    const double z = r * r;
-    double sn = fma(z, -1.0 / 39916800.0, 1.0 / 362880.0);
-    sn = fma(z, sn, -1.0 / 5040.0);
-    sn = fma(z, sn, 1.0 / 120.0);
-    sn = fma(z, sn, -1.0 / 6.0);
-    sn = fma(z * r, sn, r);
-    double cs = fma(z, 1.0 / 479001600.0, -1.0 / 3628800.0);
-    cs = fma(z, cs, 1.0 / 40320.0);
-    cs = fma(z, cs, -1.0 / 720.0);
-    cs = fma(z, cs, 1.0 / 24.0);
-    cs = fma(z, cs, -0.5);
-    cs = fma(z, cs, 1.0);
-    const int quad = (int)q & 3;
-    const float fs = (float)((quad & 1) ? cs : sn), fc = (float)((quad & 1) ? sn : cs);
-    t.s[i] = (quad & 2) ? -fs : fs;
-    t.c[i] = ((quad + 1) & 2) ? -fc : fc;
-  }
+  for (int i = 0; i < 4; ++i) rotation_cos_sin((double)pos * freq[i], t.c[i], t.s[i]);
   return t;
 }
 

@@ -4,6 +4,7 @@
   integer keys) and the ancestor walk, on NaN, infinity and tie inputs.  The kernels rank candidates by it, so
   ranks must form a permutation whatever the scores are.  If they do not,
   two candidates share a slot and another slot is never written.
+* rotation.h: cosine and sine of rotary angles against the C library's.
 * plan.h: the launch plan of every product of every configured shape and row
   count fits the kernel instantiation that it selects, and the tree
   attention's row groups divide the tree width and fit the 16 score columns.
@@ -29,6 +30,7 @@ DRIVER = r"""
 #include <cstdint>
 #include "tree_order.h"
 #include "plan.h"
+#include "rotation.h"
 using namespace prism;
 
 static float f_of(uint32_t u) { float f; std::memcpy(&f, &u, 4); return f; }
@@ -91,6 +93,12 @@ int main() {
       int nt, R, gv;
       std::scanf("%d %d %d", &nt, &R, &gv);
       std::printf("%d\n", lm_head_tiles(nt, R, gv != 0));
+    } else if (!std::strcmp(cmd, "rot")) {    // angle (hex float)
+      double a;
+      std::scanf("%la", &a);
+      float c, s;
+      rotation_cos_sin(a, c, s);
+      std::printf("%a %a\n", (double)c, (double)s);
     } else if (!std::strcmp(cmd, "sgrp")) {   // bf16 nq nkv d
       int bf, nq, nkv, d;
       std::scanf("%d %d %d %d", &bf, &nq, &nkv, &d);
@@ -176,6 +184,23 @@ def test_ancestor_walk_is_bounded_and_exact(driver):
     # corrupt parents (self loop, cycle, forward link, out of range) stop the walk
     out = driver("anc 5 0 2 1 7 -9\n")[0].split()
     assert [int(x, 16) for x in out] == [0b1, 0b10, 0b110, 0b1000, 0b10000]
+
+
+def test_rotation_is_the_angles_cos_and_sin(driver):
+    """Angles position * base^(-2 i / d): quadrant edges, negative positions,
+    positions up to 2^31 - 1, and bases below 1, whose frequencies grow until
+    the angle is more than 2^31 quarter turns.  fp64 sums rounded to fp32: half
+    an fp32 ulp, and the 1e-11 of the series and of the angle's own rounding."""
+    angles = [0.0, -0.0, 1e-30] + [k * math.pi / 4 * (1 + e) for k in range(-9, 10) for e in (0, 1e-9, -1e-9)]
+    for theta, d in ((5e5, 128), (1e4, 64), (1.0, 32), (1e-3, 64), (1e-6, 64)):
+        for i in (0, 1, d // 4, d // 2 - 1):
+            f = theta ** (-2.0 * i / d)
+            angles += [p * f for p in (1, 7, 4095, 131071, 1 << 24, (1 << 31) - 1, -5, -(1 << 31))]
+    out = driver("".join("rot %s\n" % a.hex() for a in angles))
+    for a, o in zip(angles, out):
+        c, s = (float.fromhex(x) for x in o.split())
+        tol = 2 ** -25 + 1e-10 + abs(a) * 2 ** -106
+        assert abs(c - math.cos(a)) <= tol and abs(s - math.sin(a)) <= tol, (a, c, s, math.cos(a), math.sin(a))
 
 
 def _products(cfg):
