@@ -727,7 +727,8 @@ constexpr int gemm_max_threads() { return 64 * product_max_waves(RT, NT); }
 // kernel-only epilogue tag: EPI_NORM on fusion-FC rows that the GEMV main
 // loop gathers itself (no input norm), a separate instantiation so that the
 // other EPI_NORM products carry none of the gather's registers
-constexpr int EPI_NORM_GATHER = 3;
+constexpr int EPI_NORM_GATHER = 4;
+static_assert(EPI_NORM_GATHER > EPI_STORE, "a tag of its own");
 
 template <typename T, int RT, int NT, bool PAIR, int EPI_K, int VR>
 __global__ __launch_bounds__((gemm_max_threads<RT, NT>())) void k_gemm(GemmLaunch g) {
@@ -807,12 +808,7 @@ __global__ __launch_bounds__((gemm_max_threads<RT, NT>())) void k_gemm(GemmLaunc
       const int t = g.tab_tok[r];
       if (t >= 0) tadd = *(const f32x4 *)(g.tab + (size_t)t * m.N + (t0 + n) * 16 + 4 * (lane >> 4));
     }
-    if constexpr (NP > 1 && EPI == EPI_QKV) {
-      pre = epilogue_issue<T, EPI>(g, t0 + n, r);
-      epilogue_shadow<EPI>(g, pre);
-    }
-    const float ss = epilogue_tile<T, EPI>(g, t0 + n, r, a, sc, tadd,
-                                           NP == 1 || EPI == EPI_QKV ? &pre : nullptr);
+    const float ss = epilogue_tile<T, EPI>(g, t0 + n, r, a, sc, tadd, NP == 1 ? &pre : nullptr);
     if (EPI == EPI_NORM && r < g.R && lane < 16) g.ss[(size_t)(t0 + n) * g.R + r] = ss;
   };
   if constexpr (NP > 1) {
@@ -1268,8 +1264,8 @@ static bool gemm_epi(const GemmLaunch &gl, hipStream_t s) {
   }
   if (g.epi == EPI_NORM) hipLaunchKernelGGL((k_gemm<T, RT, NT, PAIR, EPI_NORM, VR>), grid, dim3(64 * g.kw), lds, s, g);
   else if (g.epi == EPI_SWIGLU) hipLaunchKernelGGL((k_gemm<T, RT, NT, PAIR, EPI_SWIGLU, VR>), grid, dim3(64 * g.kw), lds, s, g);
-  else if constexpr (NT <= 2) hipLaunchKernelGGL((k_gemm<T, RT, NT, PAIR, EPI_QKV, VR>), grid, dim3(64 * g.kw), lds, s, g);
-  else return false;   // the planner keeps QKV off the 4- and 8-tile unsplit variants
+  else if constexpr (NT == 1) hipLaunchKernelGGL((k_gemm<T, RT, NT, PAIR, EPI_QKV, VR>), grid, dim3(64 * g.kw), lds, s, g);
+  else return false;   // the planner keeps QKV off the unsplit variants of several tiles
   return true;
 }
 
@@ -1654,7 +1650,7 @@ static bool gemm_rt(const GemmLaunch &g, hipStream_t s) {
     if (!(g.rowgrp && rows_direct(g))) finish_launch<T>(g, s);
     return true;
   }
-  if (g.R > MAX_ROWS) return false;
+  if (g.R > 32) return false;   // unsplit products hold at most 2 row tiles
   if constexpr (sizeof(T) == 2) {
     if (g.gemv) {
       if (g.R <= 1) return gemm_epi<T, 1, 1, PAIR, 1>(g, s);
@@ -1663,27 +1659,18 @@ static bool gemm_rt(const GemmLaunch &g, hipStream_t s) {
   }
   if (g.nt == 7) {          // gate/up shapes whose tile count is a multiple of 7 * 256
     if (g.R <= 16) return gemm_epi<T, 1, 7, PAIR, 0>(g, s);
-    if (g.R <= 32) return gemm_epi<T, 2, 7, PAIR, 0>(g, s);
-    return false;
+    return gemm_epi<T, 2, 7, PAIR, 0>(g, s);
   }
   if (g.nt == 8) {          // batched rows, many tiles: no K slices
     if (g.R <= 16) return gemm_epi<T, 1, 8, PAIR, 0>(g, s);
-    if (g.R <= 32) return gemm_epi<T, 2, 8, PAIR, 0>(g, s);
-    return false;
+    return gemm_epi<T, 2, 8, PAIR, 0>(g, s);
   }
   if (g.nt == 4) {
     if (g.R <= 16) return gemm_epi<T, 1, 4, PAIR, 0>(g, s);
-    if (g.R <= 32) return gemm_epi<T, 2, 4, PAIR, 0>(g, s);
-    return false;
+    return gemm_epi<T, 2, 4, PAIR, 0>(g, s);
   }
-  if (g.nt == 2) {
-    if (g.R <= 16) return gemm_epi<T, 1, 2, PAIR, 0>(g, s);
-    if (g.R <= 32) return gemm_epi<T, 2, 2, PAIR, 0>(g, s);
-    return gemm_epi<T, 4, 2, PAIR, 0>(g, s);
-  }
-  if (g.R <= 16) return gemm_epi<T, 1, 1, PAIR, 0>(g, s);
-  if (g.R <= 32) return gemm_epi<T, 2, 1, PAIR, 0>(g, s);
-  return gemm_epi<T, 4, 1, PAIR, 0>(g, s);
+  if (g.nt != 1 || g.R > GEMV_MAX_ROWS) return false;
+  return gemm_epi<T, 1, 1, PAIR, 0>(g, s);   // fp32, or rows too wide for the GEMV's LDS
 }
 
 bool launch_gemm_slices(const GemmLaunch &g, hipStream_t s) { return gemm_slices<bf16_t, true>(g, s); }

@@ -169,7 +169,7 @@ inline int unsplit_cost(int n_tiles, int nt) { return (n_tiles / nt + 255) / 256
 // Plan of a product of an [N = 16 n_tiles, K] matrix over R rows.  nkb and K
 // are those of the planned k range (the fusion FC may cover its feature
 // columns only); K_full is the width of the staged operand; qkv: the QKV
-// product (its epilogue runs on at most 2 tiles per wave); lds_limit: LDS
+// product (unsplit only at one tile per wave); lds_limit: LDS
 // bytes one workgroup may use.
 inline ProductPlan plan_product(int n_tiles, int nkb, int K, int K_full, int R, bool qkv,
                                 bool bf16, size_t lds_limit) {

@@ -241,9 +241,11 @@ def test_every_plan_fits_its_kernel(driver):
         if split == 0 and not gemv:
             assert 64 * kw <= 64 * maxw
             # instantiations the launcher dispatches unsplit
-            assert nt in (1, 2, 4, 7, 8), (case, o)
+            assert nt in (1, 4, 7, 8), (case, o)
             if nt in (4, 7, 8):
                 assert case[3] <= 32 and not case[4], (case, o)
+            else:
+                assert case[3] <= 2, (case, o)
         if split > 0:
             assert nt in (1, 2, 4, 8), (case, o)
         if gemv:
@@ -431,6 +433,8 @@ def test_plans_on_random_shapes(driver):
         size = int(out[2 * i + 1])
         assert fits == 1, (bf, nt, nkb, R, out[2 * i])
         assert rowgrp == (1 if bf and R > 64 else 0), (bf, nt, nkb, R, out[2 * i])
+        if split == 0:   # unsplit: 2 row tiles and 4, 7 or 8 tiles per wave at most
+            assert R <= 32 and tiles in (4, 7, 8), (bf, nt, nkb, R, out[2 * i])
         if split > 0:
             assert split <= nkb, (bf, nt, nkb, R, split)
             assert split * R * 16 * nt <= size, (bf, nt, nkb, R, split, size)
