@@ -256,6 +256,33 @@ inline size_t product_partial_floats(int n_tiles, int nkb, int K, int rows_max) 
   return most;
 }
 
+// The same for every product of a context: rows of a drafting pass, of one
+// chunk of a catch-up front through the staged operand (at least those of a
+// tree-scoring pass), and of one chunk of a long front, whose fusion FC and
+// k and v rows run over all of them and whose q rows over the sequences.
+struct PartialDims {
+  int hidden, ffn, feat_width, q_width, kv_width;   // kv_width: the k rows, and the v rows
+  int rows, front_rows, long_rows;
+  bool bf16;
+};
+inline size_t context_partial_floats(const PartialDims &d) {
+  size_t most = 0;
+  auto upd = [&](int N, int K, int rows_max) {
+    const size_t n = product_partial_floats(N / 16, K / (d.bf16 ? 32 : 16), K, rows_max);
+    if (n > most) most = n;
+  };
+  const int H = d.hidden;
+  upd(H, H + d.feat_width, d.long_rows);
+  upd(H, 2 * H, d.front_rows);
+  upd(d.q_width + 2 * d.kv_width, H, d.front_rows);
+  upd(2 * d.kv_width, H, d.long_rows);
+  upd(d.q_width, H, d.rows);
+  upd(H, d.q_width, d.front_rows);
+  upd(2 * d.ffn, H, d.front_rows);
+  upd(H, d.ffn, d.front_rows);
+  return most;
+}
+
 // Whether a plan's workgroup fits the instantiation it launches: its waves
 // (the launcher refuses a plan that does not) and its LDS.  K_full as in
 // plan_product.

@@ -318,19 +318,8 @@ prism_status prism_create(const prism_config *cfg, prism_ctx **out) {
   add((void **)&c->hid[0], RP * c->H * 4);
   add((void **)&c->hid[1], R * c->H * 4);
   if ((int)RF > GEMV_MAX_ROWS) {   // batched products: K-slice partial sums [split][rows][N]
-    size_t pn = 0;
-    auto upd = [&](int N, int K, size_t rmax) {
-      const TiledMat t = make_tiled(N, K, bf16);
-      pn = std::max(pn, product_partial_floats(t.n_tiles, t.nkb, t.K, (int)rmax));
-    };
-    upd(c->H, c->H + k.feat_width, RF);
-    upd(c->H, 2 * c->H, RX);
-    upd(c->QKV, c->H, RX);
-    upd(2 * c->nkv * c->d, c->H, RF);
-    upd(c->nq * c->d, c->H, R);
-    upd(c->H, c->nq * c->d, RX);
-    upd(2 * c->I, c->H, RX);
-    upd(c->H, c->I, RX);
+    const PartialDims pd{c->H, c->I, k.feat_width, c->nq * c->d, c->nkv * c->d, rows, (int)RX, (int)RF, bf16};
+    const size_t pn = context_partial_floats(pd);
     add((void **)&c->part, pn * 4);
   }
   add((void **)&c->lm_max, R * c->n_wg_lm * 4);

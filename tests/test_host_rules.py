@@ -93,6 +93,27 @@ int main() {
       int nt, R, gv;
       std::scanf("%d %d %d", &nt, &R, &gv);
       std::printf("%d\n", lm_head_tiles(nt, R, gv != 0));
+    } else if (!std::strcmp(cmd, "cpf")) {    // H I F q kv rows front long bf16
+      PartialDims d;
+      int bf;
+      std::scanf("%d %d %d %d %d %d %d %d %d", &d.hidden, &d.ffn, &d.feat_width, &d.q_width, &d.kv_width, &d.rows,
+                 &d.front_rows, &d.long_rows, &bf);
+      d.bf16 = bf != 0;
+      std::printf("%zu\n", context_partial_floats(d));
+    } else if (!std::strcmp(cmd, "tile")) {   // n_tiles nkb K R qkv: the bf16 plan's tile flag, tiles, slices
+      int nt, nkb, K, R, qkv;
+      std::scanf("%d %d %d %d %d", &nt, &nkb, &K, &R, &qkv);
+      const ProductPlan p = plan_product(nt, nkb, K, K, R, qkv != 0, true, 163840);
+      std::printf("%d %d %d %d\n", p.tile, p.rowgrp, p.nt, p.split);
+    } else if (!std::strcmp(cmd, "pb")) {     // n_tiles nkb K R: plan_batched
+      int n, nkb, K, R, nt, sp;
+      std::scanf("%d %d %d %d", &n, &nkb, &K, &R);
+      plan_batched(n, nkb, K, R, nt, sp);
+      std::printf("%d %d\n", nt, sp);
+    } else if (!std::strcmp(cmd, "rgr")) {    // n_tiles R split store
+      int n, R, sp, st;
+      std::scanf("%d %d %d %d", &n, &R, &sp, &st);
+      std::printf("%d\n", rowgrp_rows(n, R, sp, st != 0));
     } else if (!std::strcmp(cmd, "rot")) {    // angle (hex float)
       double a;
       std::scanf("%la", &a);
@@ -438,6 +459,75 @@ def test_plans_on_random_shapes(driver):
         if split > 0:
             assert split <= nkb, (bf, nt, nkb, R, split)
             assert split * R * 16 * nt <= size, (bf, nt, nkb, R, split, size)
+
+
+@pytest.mark.parametrize("max_new", [0, 40, 65, 300, 1531, 4096])
+def test_partial_buffer_holds_long_fronts_and_tree_fronts(driver, max_new):
+    """The partial buffer of a bf16 context (context_partial_floats, which
+    prism_create allocates) holds split x rows x N of every plan its calls
+    make: passes and staged fronts up to 256 rows, long fronts up to 2048 (the
+    fusion FC's feature columns and the k and v rows of the QKV product), the q
+    rows of the sequences, and the fusion FC over 1 to 64 trees' feature rows."""
+    cfgs = [c for c in CONFIGS.values() if c.dtype == "bf16"] + [
+        SMALL_BF16_CHAIN, SMALL_BF16_TREE, SMALL_BF16_CHAIN.with_(ffn=12800),
+        SMALL_BF16_CHAIN.with_(hidden=2304, feat_width=12288), SMALL_BF16_CHAIN.with_(hidden=480, feat_width=1440),
+        SMALL_BF16_CHAIN.with_(n_q_heads=1, n_kv_heads=1, head_dim=32, feat_width=32)]
+    for cfg in {(c.hidden, c.ffn, c.feat_width, c.n_q_heads, c.n_kv_heads, c.batch, c.tree_width): c
+                for c in cfgs}.values():
+        H, I, F = cfg.hidden, cfg.ffn, cfg.feat_width
+        q, kv = cfg.n_q_heads * cfg.head_dim, cfg.n_kv_heads * cfg.head_dim
+        tab = H % 64 == 0
+        rows = cfg.batch * max(1, cfg.tree_width)
+        long_rows = max(256, -(-min(max_new, 2048) // 16) * 16 if tab else 0)
+        size = int(driver("cpf %d %d %d %d %d %d 256 %d 1\n" % (H, I, F, q, kv, rows, long_rows))[0])
+        lo = H if tab else 0
+        lines, cases = [], []
+
+        def add(what, N, K, Rs, qkv=0):
+            for R in Rs:
+                lines.append("tile %d %d %d %d %d" % (N // 16, K // 32, K, R, qkv))
+                cases.append((what, N, K, R))
+        staged = range(3, 257)
+        for K in {H + F - lo, 2 * H - lo}:
+            add("fc", H, K, staged)
+        add("qkv", q + 2 * kv, H, staged, 1)
+        add("o", H, q, staged)
+        add("gate/up", 2 * I, H, staged)
+        add("down", H, I, staged)
+        if tab and max_new > 64:
+            add("long fc", H, F, range(65, min(max_new, 2048) + 1))
+            add("long kv", 2 * kv, H, range(65, min(max_new, 2048) + 1), 1)
+            add("q", q, H, range(1, rows + 1), 1)
+        out = driver("\n".join(lines) + "\n")
+        for (what, N, K, R), o in zip(cases, out):
+            tile, rowgrp, nt, split = (int(x) for x in o.split())
+            assert (tile, rowgrp) == (1 if 33 <= R <= 64 else 0, 1 if R > 64 else 0), (cfg.name, what, R, o)
+            assert split <= max(1, K // 32) and split * R * N <= size, (cfg.name, what, R, o, size)
+            if tile:
+                assert split >= 1
+        if tab:
+            trees = range(1, 65)
+            out = driver("".join("pb %d %d %d %d\n" % (H // 16, F // 32, F, R) for R in trees))
+            for R, o in zip(trees, out):
+                nt, split = (int(x) for x in o.split())
+                assert 1 <= split <= max(1, F // 32) and split * R * H <= size, (cfg.name, R, o, size)
+
+
+def test_tile_kernel_rows(driver):
+    """Rows per workgroup of the tile kernel: 64 or 128, and 256 only where the
+    kernel stores the product itself over more than 192 rows; the fewest rounds
+    of the 256 CUs by the measured costs of a round."""
+    cost = {64: 59, 128: 100, 256: 179}
+    cases = list(itertools.product((16, 128, 256, 313, 1792, 2000, 8016), (33, 64, 65, 128, 129, 183, 192, 193,
+                                                                           244, 256, 700, 2048), (1, 5, 8), (0, 1)))
+    out = driver("".join("rgr %d %d %d %d\n" % c for c in cases))
+    for (n, R, split, store), o in zip(cases, out):
+        r = int(o)
+        t = lambda k: -(-(-(-n // 16) * split * -(-R // k)) // 256) * cost[k]
+        assert r in (64, 128) or (r == 256 and store and R > 192), (n, R, split, store, r)
+        small = min((64, 128), key=t)
+        want = 256 if store and R > 192 and t(256) < min(t(64), t(128)) else small if t(64) != t(128) else 128
+        assert r == want, (n, R, split, store, r, want)
 
 
 def test_lm_head_tiles(driver):
