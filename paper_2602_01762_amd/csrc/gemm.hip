@@ -1282,7 +1282,7 @@ static bool gemm_epi(const GemmLaunch &gl, hipStream_t s) {
 //  * the activations of a k-block come as whole tiled fragments too (PK),
 //    one coalesced KiB from a uniform address (rows read from row-major
 //    memory, 16 half lines of 64 bytes per load: 8B LM head over 244 rows
-//    479 against 413 us); rows that a caller passes row-major (E, target
+//    484 against 430 us at 128 rows, 438 against 405 at 256); rows that a caller passes row-major (E, target
 //    features) are read in place;
 //  * a wave reads the next k-block's fragments while it multiplies the
 //    current one; with two planes the lo fragments of the current k-block
@@ -1739,9 +1739,9 @@ void launch_lmhead(bool bf16, const LmLaunch &g, hipStream_t s) {
 // LM head over many rows at once, logits only (the target's tree-scoring
 // pass: up to LMR_MAX_ROWS rows in one launch): the tile kernel with one K
 // slice, its epilogue storing logits[r][v] = scale[r] * acc (the final
-// RMSNorm's row scale comes precomputed).  8B, 244 rows: 449 us at 256 x 128,
-// 402 at 256 x 256 (medians of 12), which loads three fragments where two
-// workgroups of the former load four.
+// RMSNorm's row scale comes precomputed).  8B, 244 rows: 430 us at 256 x 128,
+// 405 at 256 x 256, which loads three fragments where two workgroups of the
+// former load four.
 bool launch_lmhead_rows(const LmRowsArgs &a, hipStream_t s) {
   GemmLaunch g{};
   g.m = a.m;

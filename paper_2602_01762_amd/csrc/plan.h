@@ -98,17 +98,15 @@ inline int rowgrp_split(int n_tiles, int nkb, int R) {
 
 // Rows per workgroup (128 or 64, and 256 where the kernel stores the product
 // itself) of a row-group product: whichever takes fewer rounds of the 256
-// CUs, a 64-row round costing 0.59 of a 128-row one (8B LM head over 244 rows,
-// 501 tile groups: 489 us in 8 rounds against 413 us in 4) and a 256-row round
-// 1.79 (402 us in 2 rounds against 449 in 4).  Up to TILE256_ABOVE rows the
-// 128-row tiles' repeated last rows cost little and gain nothing (183 rows:
-// 391 us at 256 rows against 389).
-constexpr int TILE256_ABOVE = 192;
+// CUs, a round of 64-row workgroups costing 0.59 of a 128-row one and one of
+// 256-row ones 1.87 (8B LM head over 244 rows, 501 tile groups, one run: 505
+// us in 8 rounds, 430 in 4 and 405 in 2).  256 rows are taken above 192 only:
+// below, at most three 64-row rounds (1.77) do for each 256-row one.
 inline int rowgrp_rows(int n_tiles, int R, int split, bool store = false) {
   const long xg = (long)((n_tiles + ROWGRP_TILES - 1) / ROWGRP_TILES) * split;
   const long r256 = (xg * ((R + 255) / 256) + 255) / 256;
   const long r128 = (xg * ((R + 127) / 128) + 255) / 256, r64 = (xg * ((R + 63) / 64) + 255) / 256;
-  if (store && R > TILE256_ABOVE && r256 * 179 < r128 * 100 && r256 * 179 < r64 * 59) return 256;
+  if (store && r256 * 187 < r128 * 100 && r256 * 187 < r64 * 59) return 256;
   return r64 * 59 < r128 * 100 ? 64 : 128;
 }
 

@@ -517,7 +517,7 @@ def test_tile_kernel_rows(driver):
     """Rows per workgroup of the tile kernel: 64 or 128, and 256 only where the
     kernel stores the product itself over more than 192 rows; the fewest rounds
     of the 256 CUs by the measured costs of a round."""
-    cost = {64: 59, 128: 100, 256: 179}
+    cost = {64: 59, 128: 100, 256: 187}
     cases = list(itertools.product((16, 128, 256, 313, 1792, 2000, 8016), (33, 64, 65, 128, 129, 183, 192, 193,
                                                                            244, 256, 700, 2048), (1, 5, 8), (0, 1)))
     out = driver("".join("rgr %d %d %d %d\n" % c for c in cases))
@@ -526,7 +526,7 @@ def test_tile_kernel_rows(driver):
         t = lambda k: -(-(-(-n // 16) * split * -(-R // k)) // 256) * cost[k]
         assert r in (64, 128) or (r == 256 and store and R > 192), (n, R, split, store, r)
         small = min((64, 128), key=t)
-        want = 256 if store and R > 192 and t(256) < min(t(64), t(128)) else small if t(64) != t(128) else 128
+        want = 256 if store and t(256) < min(t(64), t(128)) else small if t(64) != t(128) else 128
         assert r == want, (n, R, split, store, r, want)
 
 
