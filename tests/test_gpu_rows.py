@@ -61,6 +61,24 @@ def test_long_catchup_flags_bad_tokens():
     dr.close()
 
 
+def test_long_catchup_flags_malformed_offsets():
+    """A sequence without rows in a front of more than 64: its last row reads as
+    zeros, the flag is the offsets', and a later call is clean."""
+    cfg = SMALL_BF16_CHAIN.with_(name="small_catchup_badoff", batch=3, n_new=(30, 30), n_steps=1)
+    dr, w, inp = gpu_setup(cfg)
+    good = inp.new_offsets.clone()
+    inp.new_offsets = torch.tensor([0, 50, 50, 90], dtype=torch.int32, device="cuda")
+    dr.chain_catchup(inp)
+    assert dr.device_status() == -1
+    inp.new_offsets = good
+    out = dr.chain_catchup(inp, logits=True, hidden=True)
+    torch.cuda.synchronize()
+    assert dr.device_status() == 0
+    orc, hi = oracle_for(cfg, w, inp, [0, 2])
+    check_chain(cfg, out, orc, hi, [0, 2], catchup=True, inp=inp)
+    dr.close()
+
+
 def test_long_front_sums_stay_short():
     """2048 accepted rows at hidden 2304: one K slice of 384 k-blocks of the
     fusion FC.  All terms positive, so the running sum grows steadily and each
