@@ -150,9 +150,11 @@ def pass_rows(cfg, k):
 
 VERIFY_WORKLOADS = {
     # the verification step of Sec. 2 on synthetic target logits, 8B vocabulary
-    "verify_bs16": dict(mode="chain", batch=16, K=5, temperature=1.0),
-    "verify_bs16_greedy": dict(mode="chain", batch=16, K=5, temperature=0.0),
-    "verify_tree_bs4": dict(mode="tree", batch=4, nodes=60),
+    "verify_bs16": dict(mode="chain", batch=16, K=5, temperature=1.0,
+                        kernels="k_rows_soft + k_verify_decide + k_verify_draw"),
+    "verify_bs16_greedy": dict(mode="chain", batch=16, K=5, temperature=0.0,
+                               kernels="k_rows_best + k_verify_greedy"),
+    "verify_tree_bs4": dict(mode="tree", batch=4, nodes=60, kernels="k_rows_best + k_verify_tree"),
 }
 
 
@@ -202,7 +204,7 @@ def verify_bench(args):
            "ms_per_step": round(us / 1e3, 5), "higher_is_better": False, "scaling": "weak",
            "vs_baseline": None, "dtype": "f32", "data": "synthetic target / draft logits",
            "config": {"workload": name, "batch": B, "vocab": V},
-           "roofline": {"kernel": "k_rows_stats + k_verify_* (logits stream)", "bound": "hbm",
+           "roofline": {"kernel": spec["kernels"] + " (logits stream)", "bound": "hbm",
                         "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": None,
                         "algorithmic_bytes_per_launch": nbytes}}

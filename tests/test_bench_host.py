@@ -80,3 +80,13 @@ def test_mfma_figures():
     H, I, V = 8192, 28672, 128256
     params = H * 2 * H + (64 + 16) * 128 * H + H * 64 * 128 + 3 * H * I + V * H
     assert bench.product_flops(L3_70B_BS32, 1, 32) == 2 * 32 * params
+
+
+def test_reported_kernels_exist():
+    """Every kernel that the benchmark names is one of the library's."""
+    import glob
+    import re
+    src = "".join(open(f).read() for f in glob.glob(os.path.join(ROOT, "paper_2602_01762_amd", "csrc", "*.hip")))
+    defined = set(re.findall(r"\b(k_\w+)\s*\(", src))
+    named = set(re.findall(r"\bk_[a-z]\w*", open(os.path.join(ROOT, "bench.py")).read())) - {"k_lmhead_traffic"}
+    assert named and named <= defined, sorted(named - defined)
