@@ -278,9 +278,11 @@ prism_status prism_draft_chain_sample(prism_ctx *ctx, const prism_batch *batch,
  * prism_device_status and leaves the outputs unspecified).  Outputs as in
  * prism_draft_chain; d_out_logits and d_out_hidden hold the last row's
  * values for step 1.  Requires max_new_rows >= total_rows.  The fusion FC
- * and QKV of the accepted rows run in chunks of up to 64 rows (a row's KV
- * depends on no other row, and the attention runs once every chunk has
- * written its KV), so a call may take more rows than one pass. */
+ * and QKV of the accepted rows run in chunks (of up to 256 rows, and of up to
+ * 2048 above 64 rows in a bf16 context with embedding tables and features at
+ * a 16-byte aligned address; a row's KV depends on no other row, and the
+ * attention runs once every chunk has written its KV), so a call may take
+ * more rows than one pass. */
 prism_status prism_draft_chain_catchup(prism_ctx *ctx, const prism_batch *batch,
                                        const prism_catchup *catchup, int32_t K,
                                        int32_t *d_out_tokens, float *d_out_logits,
