@@ -113,6 +113,47 @@ def test_long_front_sums_stay_short():
     dr.close()
 
 
+# k-blocks of the one slice of the front's fusion FC: at, below and past one and
+# two running sums of 32, and fewer than the loads in flight
+@pytest.mark.parametrize("kblocks", [1, 3, 31, 32, 33, 34, 64, 65])
+def test_long_front_running_sum_edges(kblocks):
+    """2048 accepted rows at hidden 2304, random values: the FC's output in the
+    last row (W_o, W_down and E zero) against fp64.  The features are one exact
+    plane, so the error is fp32 rounding: each of up to 34 additions, of the
+    sum's size times 2^-24, over a sum of F terms of size sqrt(F)."""
+    H, F, T = 2304, 32 * kblocks, 2048
+    cfg = SMALL_BF16_CHAIN.with_(name="small_fold_%d" % kblocks, hidden=H, feat_width=F, batch=1, n_new=(T, T),
+                                 n_steps=1, n_sets=1, f_map=(0,), ctx_range=(0, 0))
+    from paper_2602_01762_amd import Drafter
+    w, inp = make_weights(cfg, "cuda"), make_inputs(cfg, "cuda")
+    ps = w.sets[0]
+    for t in (ps.w_o, ps.w_down, w.embed):
+        t.zero_()
+    dr = Drafter(cfg)
+    dr.load(w)
+    out = dr.chain_catchup(inp, hidden=True)
+    torch.cuda.synchronize()
+    assert dr.device_status() == 0
+    want = ps.w_fc[:, H:].double().cpu().numpy() @ inp.new_features[-1].double().cpu().numpy()
+    err = out["hidden"][0, 0].double().cpu().numpy() - want
+    assert np.max(np.abs(err)) <= 34 * 2 ** -24 * 0.02 * F ** 0.5 * 5     # 5 sigma of the largest of 2304
+    dr.close()
+
+
+# one slice of 15, 16, 17 and 33 k-blocks at 64 rows (running sums of 16)
+@pytest.mark.parametrize("hidden", [480, 512, 544, 1056])
+def test_chain_running_sum_edges(hidden):
+    cfg = SMALL_BF16_CHAIN.with_(name="small_fold64_%d" % hidden, batch=40, hidden=hidden, ffn=16416, n_steps=2,
+                                 ctx_range=(1, 60))
+    dr, w, inp = gpu_setup(cfg)
+    out = dr.chain(inp, logits=True, hidden=True)
+    torch.cuda.synchronize()
+    assert dr.device_status() == 0
+    orc, hi = oracle_for(cfg, w, inp, [0, 39])
+    log(cfg.name, check_chain(cfg, out, orc, hi, [0, 39], inp=inp))
+    dr.close()
+
+
 # trees x (nodes + 1) rows: one tree below the small kernels' limit, whole
 # row tiles, one row past a tile, passes of whole trees; 1 node: 2 rows share
 # a feature row; hidden 480: no embedding table; vocabulary 33040: more than
